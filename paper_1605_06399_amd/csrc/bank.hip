@@ -620,13 +620,13 @@ __device__ __forceinline__ void bank_fwd_pers_body(const float* __restrict__ x, 
         const int n = t / tiles_img, ti = t - n * tiles_img;
         int x0, y0;
         tile_origin(ti, tiles_x, BT, BT, x0, y0);
-        st.load(x + (size_t)n * hw, (size_t)W * 4, W, H, x0 - RA, y0 - R, vec);
+        st.load(x + (size_t)n * hw, (size_t)W * 4, W, H, x0 - RA, y0 - R);
     };
     const BandWalk walk(tiles_x, ntiles / tiles_x);   // images stacked vertically
     int t = walk.tile(0);
     if (t >= 0) {
         fetch(t);
-        st.store(s[0]);
+        st.store(s[0], W, H);
     }
     __syncthreads();
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
@@ -651,7 +651,7 @@ __device__ __forceinline__ void bank_fwd_pers_body(const float* __restrict__ x, 
             }
             // stage the next tile before this tile's first output store: the wait on the
             // prefetch loads then never includes stores
-            if (f == 0 && tn >= 0) st.store(s[cur ^ 1]);
+            if (f == 0 && tn >= 0) st.store(s[cur ^ 1], W, H);
             if constexpr (SSE) sse_block(gy ? gy + plane : nullptr, y ? y + plane : nullptr, W, H, x0, y0, vec, acc, tv, sq);
             else store_block(y + plane, W, H, x0, y0, vec, acc);
         }
@@ -682,6 +682,58 @@ __global__ __launch_bounds__(256) void bank_fwd_sse_tpre_k(const float* __restri
     bank_fwd_pers_body<R, true, true>(x, w, y, tg, gy, part, F, H, W, tiles_x, tiles_img, ntiles, vec);
 }
 
+// Register stage of NR rows x LW columns of a W-wide float32 plane extended by zero.  `vec`: rows 16-byte
+// aligned (x a multiple of 4), so a chunk is wholly inside a row (one vector load), wholly outside, or
+// straddles its right end (per element).  (Loading edge tiles from clamped addresses and zeroing at the
+// LDS write, as Stage does, made the input adjoint slower: 1.24 against 1.39 ms at 32 x 16 x 1024^2, r = 4.)
+template <int NR, int LW>
+struct ZeroStage {
+    static constexpr int C4 = LW / 4;
+    static constexpr int N = (NR * C4 + 255) / 256;
+    v4f v[N];
+
+    __device__ __forceinline__ static v4f chunk(const float* __restrict__ row, int W, int x, bool vec) {
+        if (vec && x >= 0 && x + 4 <= W) return *reinterpret_cast<const v4f*>(row + x);
+        if (vec && (x + 4 <= 0 || x >= W)) return mk4(0.f, 0.f, 0.f, 0.f);
+        v4f e;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[q] = (x + q < 0 || x + q >= W) ? 0.f : row[clampi(x + q, W)];
+        return e;
+    }
+
+    __device__ __forceinline__ void load(const float* __restrict__ src, int W, int H, int gx0, int gy0, bool vec) {
+        const bool inside = vec && gx0 >= 0 && gx0 + LW <= W && gy0 >= 0 && gy0 + NR <= H;
+        if (inside) {   // no branch between the loads: all in flight together
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const int idx = (int)threadIdx.x + 256 * k;
+                if (N * 256 != NR * C4 && idx >= NR * C4) break;
+                const int rr = idx / C4, c4 = idx - rr * C4;
+                v[k] = *reinterpret_cast<const v4f*>(src + (size_t)(gy0 + rr) * W + (gx0 + 4 * c4));
+            }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int idx = (int)threadIdx.x + 256 * k;
+            if (N * 256 != NR * C4 && idx >= NR * C4) break;
+            const int rr = idx / C4, c4 = idx - rr * C4, yy = gy0 + rr;
+            if (yy < 0 || yy >= H) v[k] = mk4(0.f, 0.f, 0.f, 0.f);
+            else v[k] = chunk(src + (size_t)yy * W, W, gx0 + 4 * c4, vec);
+        }
+    }
+
+    __device__ __forceinline__ void store(float* __restrict__ s) const {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int idx = (int)threadIdx.x + 256 * k;
+            if (N * 256 != NR * C4 && idx >= NR * C4) break;
+            const int rr = idx / C4, c4 = idx - rr * C4;
+            lds4(&s[rr * LW + 4 * c4], v[k]);
+        }
+    }
+};
+
 template <int R>
 __global__ __launch_bounds__(256) void bank_bwd_in_pers_k(const float* __restrict__ gy, const float* __restrict__ w,
                                                           float* __restrict__ gx, int F, int H, int W, int tiles_x,
@@ -693,12 +745,12 @@ __global__ __launch_bounds__(256) void bank_bwd_in_pers_k(const float* __restric
     __shared__ __attribute__((aligned(16))) float wl[PERS_FMAX * N * NP];
     taps_to_lds<R, true>(w, F, wl);
     const size_t hw = (size_t)H * W;
-    Stage<F32, NR, LW, true> st;   // zero outside the image: gy is extended by zero
+    ZeroStage<NR, LW> st;   // zero outside the image: gy is extended by zero
     auto fetch = [&](int t, int f) {
         const int n = t / tiles_img, ti = t - n * tiles_img;
         int x0, y0;
         tile_origin(ti, tiles_x, BT, BT, x0, y0);
-        st.load(gy + ((size_t)n * F + f) * hw, (size_t)W * 4, W, H, x0 - RA, y0 - R, vec);
+        st.load(gy + ((size_t)n * F + f) * hw, W, H, x0 - RA, y0 - R, vec);
     };
     const BandWalk walk(tiles_x, ntiles / tiles_x);   // images stacked vertically
     int t = walk.tile(0);

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void sep_batched_k(const DevImage* __restrict_
         sep_row_pass<R, BTH, BCX>(in_s, t_s, d.tx);                                              \
         __syncthreads();                                                                         \
         if (tn < ntiles) rs.store(in_s, BTH + 2 * nd.r, (TW + 2 * ((nd.r + 3) & ~3)) / 4);       \
-        sep_col_pass<T, R, BTH, BCX>(t_s, d.dst, d.dp, d.W, d.H, d.ty, bt.x0, bt.y0, d.vec_out); \
+        sep_col_pass<T, R, BTH, BCX>(t_s, d.dst, d.dp, d.W, d.H, d.ty, bt.x0, bt.y0); \
         break;
             ICL_BATCH_CASE(0)
             ICL_BATCH_CASE(1)
@@ -120,8 +120,7 @@ __global__ __launch_bounds__(64) void sep_batched_strip_k(const DevImage* __rest
         switch (it.r) {
 #define ICL_STRIP_CASE(R)                                                                                   \
     case R:                                                                                                 \
-        sep_strip_body<T, R, STH>(d.src, d.sp, d.dst, d.dp, d.W, d.H, d.tx, d.ty, it.xs, it.y0, d.vec_ok != 0, \
-                                  d.vec_out != 0);                                                          \
+        sep_strip_body<T, R, STH>(d.src, d.sp, d.dst, d.dp, d.W, d.H, d.tx, d.ty, it.xs, it.y0);                                                          \
         break;
             ICL_STRIP_CASE(0)
             ICL_STRIP_CASE(1)
@@ -363,7 +362,6 @@ icl_status icl_batch_plan_create(const icl_image_desc* descs, int count, icl_dty
         di.src = d.src; di.dst = d.dst; di.sp = d.src_pitch; di.dp = d.dst_pitch;
         di.tx = d.taps_x; di.ty = d.taps_y; di.W = d.width; di.H = d.height; di.r = d.radius;
         di.vec_ok = ((uintptr_t)d.src % al == 0) && (d.src_pitch % al == 0);
-        di.vec_out = ((uintptr_t)d.dst % al == 0) && (d.dst_pitch % al == 0);
         const size_t ext = (size_t)(d.height - 1) * d.src_pitch + (size_t)d.width * es;
         di.src_bytes = ext < ((size_t)1 << 31) ? (unsigned)ext : 0u;
         imgs.push_back(di);

@@ -79,7 +79,7 @@ template <int R, int PX, int PY> struct Tile2d {
 template <class T, int R, int PX, int PY, int ORD>
 __global__ __launch_bounds__(256) void conv2d_lds(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                   size_t dp, int W, int H, const float* __restrict__ w,
-                                                  int tiles_x, int vec_ok, Border bd) {
+                                                  int tiles_x, Border bd) {
     using G = Tile2d<R, PX, PY>;
     constexpr int TW = G::TW, TH = G::TH, RA = G::RA, LW = G::LW, NR = G::NR, WIN = G::WIN;
     constexpr int N = 2 * R + 1;
@@ -89,36 +89,9 @@ __global__ __launch_bounds__(256) void conv2d_lds(const void* __restrict__ src, 
     const int x0 = (int)(t % (unsigned)tiles_x) * TW;
     const int y0 = (int)(t / (unsigned)tiles_x) * TH;
 
-    if (vec_ok && x0 - RA >= 0 && x0 + TW + RA <= W) {
-        // all loads first (rows clamped), then the constant rows and the LDS writes: a
-        // load-then-write loop would wait on each load in turn
-        constexpr int C4 = LW / 4, NCH = NR * C4, PER = (NCH + 255) / 256;
-        v4f v[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int idx = tid + 256 * i;
-            if (NCH % 256 != 0 && idx >= NCH) break;
-            const int rr = idx / C4, c4 = idx - rr * C4;
-            v[i] = load4<T>(src, (size_t)clampi(y0 - R + rr, H) * sp + (size_t)(x0 - RA + 4 * c4) * T::size);
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int idx = tid + 256 * i;
-            if (NCH % 256 != 0 && idx >= NCH) break;
-            const int rr = idx / C4, c4 = idx - rr * C4;
-            const int yy = y0 - R + rr;
-            if (bd.constant && (yy < 0 || yy >= H)) v[i] = mk4(bd.value, bd.value, bd.value, bd.value);
-            lds4(&in_s[rr * LW + 4 * c4], v[i]);
-        }
-    } else {
-        for (int idx = tid; idx < NR * LW; idx += 256) {
-            const int rr = idx / LW, c = idx - rr * LW;
-            const int yy = y0 - R + rr, xx = x0 - RA + c;
-            in_s[rr * LW + c] = (bd.constant && (yy < 0 || yy >= H || xx < 0 || xx >= W))
-                                    ? bd.value
-                                    : load_px<T>(src, (size_t)clampi(yy, H) * sp + (size_t)clampi(xx, W) * T::size);
-        }
-    }
+    Stage<T, NR, LW> st;   // every load is issued before any is written to LDS
+    st.load(src, sp, W, H, x0 - RA, y0 - R);
+    st.store(in_s, W, H, bd);
     __syncthreads();
 
     const int tx = tid & 15, ty = tid >> 4;
@@ -183,7 +156,7 @@ __global__ __launch_bounds__(256) void conv2d_lds(const void* __restrict__ src, 
         const int y = y0 + ty * PY + py;
         if (y >= H) break;
         const size_t row = (size_t)y * dp;
-        if (vec_ok && xb + PX <= W && PX % 4 == 0) {
+        if (xb + PX <= W && PX % 4 == 0) {
 #pragma unroll
             for (int px = 0; px < PX; px += 4)
                 store4<T>(dst, row + (size_t)(xb + px) * T::size,
@@ -201,11 +174,8 @@ hipError_t launch_lds_TR(const Conv2dArgs& a) {
     using G = Tile2d<R, PX, PY>;
     const int tiles_x = (a.W + G::TW - 1) / G::TW;
     const int tiles_y = (a.H + G::TH - 1) / G::TH;
-    const size_t al = 4 * (size_t)T::size;
-    const int vec_ok = ((uintptr_t)a.src % al == 0) && (a.sp % al == 0) && ((uintptr_t)a.dst % al == 0) &&
-                       (a.dp % al == 0);
     hipLaunchKernelGGL((conv2d_lds<T, R, PX, PY, ORD>), dim3(tiles_x * tiles_y), dim3(256), 0, a.st, a.src, a.sp,
-                       a.dst, a.dp, a.W, a.H, a.taps, tiles_x, vec_ok, a.bd);
+                       a.dst, a.dp, a.W, a.H, a.taps, tiles_x, a.bd);
     return hipGetLastError();
 }
 
@@ -245,7 +215,7 @@ bool supports_lds(const Conv2dArgs& a) { return a.r >= 0 && a.r <= 7; }
 template <class T, int R, int PX, int PY>
 __global__ __launch_bounds__(256) void conv2d_pers(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                    size_t dp, int W, int H, const float* __restrict__ w, int tiles_x,
-                                                   int tiles_y, int vec_ok, Border bd) {
+                                                   int tiles_y, Border bd) {
     using G = Tile2d<R, PX, PY>;
     constexpr int TW = G::TW, TH = G::TH, RA = G::RA, LW = G::LW, NR = G::NR;
     constexpr int N = 2 * R + 1, NP = (N + 3) & ~3;
@@ -259,8 +229,8 @@ __global__ __launch_bounds__(256) void conv2d_pers(const void* __restrict__ src,
     if (t < 0) return;
     int x0, y0;
     tile_origin(t, tiles_x, TW, TH, x0, y0);
-    st.load(src, sp, W, H, x0 - RA, y0 - R, vec_ok, bd);
-    st.store(s);
+    st.load(src, sp, W, H, x0 - RA, y0 - R);
+    st.store(s, W, H, bd);
     __syncthreads();
     const int tx = tid & 15, ty = tid >> 4;
     for (int k = 0; t >= 0; ++k) {
@@ -268,7 +238,7 @@ __global__ __launch_bounds__(256) void conv2d_pers(const void* __restrict__ src,
         if (tn >= 0) {
             int nx0, ny0;
             tile_origin(tn, tiles_x, TW, TH, nx0, ny0);
-            st.load(src, sp, W, H, nx0 - RA, ny0 - R, vec_ok, bd);
+            st.load(src, sp, W, H, nx0 - RA, ny0 - R);
         }
         float acc[PY][PX];
 #pragma unroll
@@ -277,14 +247,14 @@ __global__ __launch_bounds__(256) void conv2d_pers(const void* __restrict__ src,
             for (int px = 0; px < PX; ++px) acc[py][px] = 0.f;
         corr_rows<R, PX, PY, LW>(&s[(ty * PY) * LW + tx * PX], wl, acc);
         __syncthreads();                 // every lane is done reading s
-        if (tn >= 0) st.store(s);        // waits on the prefetch loads only: no output store issued yet
+        if (tn >= 0) st.store(s, W, H, bd);        // waits on the prefetch loads only: no output store issued yet
         const int xb = x0 + tx * PX;
 #pragma unroll
         for (int py = 0; py < PY; ++py) {
             const int y = y0 + ty * PY + py;
             if (y >= H) break;
             const size_t row = (size_t)y * dp;
-            if (vec_ok && xb + PX <= W) {
+            if (xb + PX <= W) {
 #pragma unroll
                 for (int px = 0; px < PX; px += 4)
                     store4<T>(dst, row + (size_t)(xb + px) * T::size,
@@ -307,13 +277,10 @@ hipError_t launch_pers_TR(const Conv2dArgs& a) {
     const int tiles_x = (a.W + G::TW - 1) / G::TW;
     const int tiles_y = (a.H + G::TH - 1) / G::TH;
     const int ntiles = tiles_x * tiles_y;
-    const size_t al = 4 * (size_t)T::size;
-    const int vec_ok = ((uintptr_t)a.src % al == 0) && (a.sp % al == 0) && ((uintptr_t)a.dst % al == 0) &&
-                       (a.dp % al == 0);
     const void* k = reinterpret_cast<const void*>(&conv2d_pers<T, R, PX, PY>);
     const int grid = persistent_grid(k, 256, ntiles);
     hipLaunchKernelGGL((conv2d_pers<T, R, PX, PY>), dim3(grid), dim3(256), 0, a.st, a.src, a.sp, a.dst, a.dp, a.W,
-                       a.H, a.taps, tiles_x, tiles_y, vec_ok, a.bd);
+                       a.H, a.taps, tiles_x, tiles_y, a.bd);
     return hipGetLastError();
 }
 

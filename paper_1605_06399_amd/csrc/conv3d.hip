@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void sep3_stream(const void* __restrict__ src,
                                                    void* __restrict__ dst, size_t drp, size_t dsp, int W, int H,
                                                    int D, const float* __restrict__ tx, const float* __restrict__ ty,
                                                    const float* __restrict__ tz, int tiles_x, int tiles_xy,
-                                                   int vec_ok, int vec_out, Border bd) {
+                                                   Border bd) {
     using G = SepTile<R, 16, 1>;
     constexpr int TW = G::TW, RA = G::RA, LW = G::LW, NR = G::NR;
     constexpr int KZ = TZ + 2 * R;   // input slices walked
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void sep3_stream(const void* __restrict__ src,
             st.fill(bd.value);
         } else {
             const char* base = static_cast<const char*>(src) + (size_t)clampi(z, D) * ssp;
-            st.load(base, srp, W, H, x0 - RA, y0 - R, vec_ok, bd);
+            st.load(base, srp, W, H, x0 - RA, y0 - R);
         }
     };
     // lane: columns 4g .. 4g+3 of tile row rg (16 column groups x 16 rows)
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void sep3_stream(const void* __restrict__ src,
     static_for<KZ>([&](auto k_c) {
         constexpr int kz = decltype(k_c)::value;
         __syncthreads();                      // the previous slice's row pass is done with in_s
-        st.store(in_s);
+        st.store(in_s, W, H, bd);
         if constexpr (kz + 1 < KZ) load_slice(kz + 1);   // next slice in flight during this one
         __syncthreads();
         sep_row_pass<R, 16, 1>(in_s, t_s, tx);
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void sep3_stream(const void* __restrict__ src,
             if (z < D && y < H) {
                 const size_t row = (size_t)z * dsp + (size_t)y * drp;
                 const v4f a = acc[slot];
-                if (vec_out && x + 4 <= W) {
+                if (x + 4 <= W) {
                     store4<T>(dst, row + (size_t)x * T::size, a);
                 } else {
                     if (x < W) store_px<T>(dst, row + (size_t)x * T::size, a.x);
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void sep3_stream2(const void* __restrict__ src
                                                     void* __restrict__ dst, size_t drp, size_t dsp, int W, int H,
                                                     int D, const float* __restrict__ tx, const float* __restrict__ ty,
                                                     const float* __restrict__ tz, int tiles_x, int tiles_xy,
-                                                    int vec_ok, int vec_out, Border bd) {
+                                                    Border bd) {
     using G = SepTile<R, TH, 1>;
     constexpr int TW = G::TW, RA = G::RA, LW = G::LW, NR = G::NR, PY = TH / 16;
     constexpr int KZ = TZ + 2 * R;   // input slices walked
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) void sep3_stream2(const void* __restrict__ src
             st.fill(bd.value);
         } else {
             const char* base = static_cast<const char*>(src) + (size_t)clampi(z, D) * ssp;
-            st.load(base, srp, W, H, x0 - RA, y0 - R, vec_ok, bd);
+            st.load(base, srp, W, H, x0 - RA, y0 - R);
         }
     };
     const int g = threadIdx.x % 16, rg = threadIdx.x / 16;
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void sep3_stream2(const void* __restrict__ src
 #pragma unroll
         for (int p = 0; p < PY; ++p) acc[k][p] = mk4(0.f, 0.f, 0.f, 0.f);
     load_slice(0);
-    st.store(in_s[0]);
+    st.store(in_s[0], W, H, bd);
     if constexpr (KZ > 1) load_slice(1);
     __syncthreads();
     static_for<KZ>([&](auto k_c) {
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void sep3_stream2(const void* __restrict__ src
             }
         }
         if constexpr (kz + 1 < KZ) {
-            st.store(in_s[cur ^ 1]);
+            st.store(in_s[cur ^ 1], W, H, bd);
             if constexpr (kz + 2 < KZ) load_slice(kz + 2);   // in flight during the next slice
         }
         // z pass: input slice kz feeds output slices kz - k, k = 0 .. 2r
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void sep3_stream2(const void* __restrict__ src
                 if (z < D && y < H) {
                     const size_t row = (size_t)z * dsp + (size_t)y * drp;
                     const v4f a = acc[slot][p];
-                    if (vec_out && x + 4 <= W) {
+                    if (x + 4 <= W) {
                         store4<T>(dst, row + (size_t)x * T::size, a);
                     } else {
                         if (x < W) store_px<T>(dst, row + (size_t)x * T::size, a.x);
@@ -321,12 +321,8 @@ hipError_t launch_stream2_TR(const Sep3Args& a) {
     const int tiles_x = (a.W + 63) / 64, tiles_y = (a.H + TH - 1) / TH, zb = (a.D + TZ - 1) / TZ;
     const long long blocks = (long long)tiles_x * tiles_y * zb;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t al = 4 * (size_t)T::size;
-    const int vec_ok = ((uintptr_t)a.src % al == 0) && (a.srp % al == 0) && (a.ssp % al == 0);
-    const int vec_out = ((uintptr_t)a.dst % al == 0) && (a.drp % al == 0) && (a.dsp % al == 0);
     hipLaunchKernelGGL((sep3_stream2<T, R, TZ, TH>), dim3((unsigned)blocks), dim3(256), 0, a.st, a.src, a.srp,
-                       a.ssp, a.dst, a.drp, a.dsp, a.W, a.H, a.D, a.tx, a.ty, a.tz, tiles_x, tiles_x * tiles_y,
-                       vec_ok, vec_out, a.bd);
+                       a.ssp, a.dst, a.drp, a.dsp, a.W, a.H, a.D, a.tx, a.ty, a.tz, tiles_x, tiles_x * tiles_y, a.bd);
     return hipGetLastError();
 }
 
@@ -355,12 +351,8 @@ hipError_t launch_stream_TR(const Sep3Args& a) {
     const int tiles_x = (a.W + 63) / 64, tiles_y = (a.H + 15) / 16, zb = (a.D + TZ - 1) / TZ;
     const long long blocks = (long long)tiles_x * tiles_y * zb;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t al = 4 * (size_t)T::size;
-    const int vec_ok = ((uintptr_t)a.src % al == 0) && (a.srp % al == 0) && (a.ssp % al == 0);
-    const int vec_out = ((uintptr_t)a.dst % al == 0) && (a.drp % al == 0) && (a.dsp % al == 0);
     hipLaunchKernelGGL((sep3_stream<T, R, TZ>), dim3((unsigned)blocks), dim3(256), 0, a.st, a.src, a.srp, a.ssp,
-                       a.dst, a.drp, a.dsp, a.W, a.H, a.D, a.tx, a.ty, a.tz, tiles_x, tiles_x * tiles_y, vec_ok,
-                       vec_out, a.bd);
+                       a.dst, a.drp, a.dsp, a.W, a.H, a.D, a.tx, a.ty, a.tz, tiles_x, tiles_x * tiles_y, a.bd);
     return hipGetLastError();
 }
 

@@ -110,15 +110,13 @@ namespace {
 template <class T, int R, int TH, int CX>
 __global__ __launch_bounds__(256) void sep_fused(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                  size_t dp, int W, int H, const float* __restrict__ tx,
-                                                 const float* __restrict__ ty, int tiles_x, int vec_ok, int vec_out,
-                                                 Border bd) {
+                                                 const float* __restrict__ ty, int tiles_x, Border bd) {
     using G = SepTile<R, TH, CX>;
     __shared__ __attribute__((aligned(16))) float lds[G::LDS_FLOATS];
     const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
     const int x0 = (int)(t % (unsigned)tiles_x) * G::TW;
     const int y0 = (int)(t / (unsigned)tiles_x) * TH;
-    const bool vec = vec_ok && x0 - G::RA >= 0 && x0 + G::TW + G::RA <= W;
-    sep_tile_body<T, R, TH, CX>(src, sp, dst, dp, W, H, tx, ty, x0, y0, vec, vec_out, lds, bd);
+    sep_tile_body<T, R, TH, CX>(src, sp, dst, dp, W, H, tx, ty, x0, y0, lds, bd);
 }
 
 template <class T, int R, int TH, int CX>
@@ -126,11 +124,8 @@ hipError_t launch_fused_TR(const SepArgs& a) {
     using G = SepTile<R, TH, CX>;
     const int tiles_x = (a.W + G::TW - 1) / G::TW;
     const int tiles_y = (a.H + TH - 1) / TH;
-    const size_t vec_align = 4 * (size_t)T::size;
-    const int vec_ok = ((uintptr_t)a.src % vec_align == 0) && (a.sp % vec_align == 0);
-    const int vec_out = ((uintptr_t)a.dst % vec_align == 0) && (a.dp % vec_align == 0);
     hipLaunchKernelGGL((sep_fused<T, R, TH, CX>), dim3(tiles_x * tiles_y), dim3(256), 0, a.st, a.src, a.sp,
-                       a.dst, a.dp, a.W, a.H, a.tx, a.ty, tiles_x, vec_ok, vec_out, a.bd);
+                       a.dst, a.dp, a.W, a.H, a.tx, a.ty, tiles_x, a.bd);
     return hipGetLastError();
 }
 
@@ -166,8 +161,8 @@ bool supports_fused(const SepArgs& a) { return a.r >= 0 && a.r <= 7; }
 template <class T, int R, int TH, int CX>
 __global__ __launch_bounds__(256) void sep_pers(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                 size_t dp, int W, int H, const float* __restrict__ tx,
-                                                const float* __restrict__ ty, int tiles_x, int tiles_y, int vec_ok,
-                                                int vec_out, Border bd) {
+                                                const float* __restrict__ ty, int tiles_x, int tiles_y,
+                                                Border bd) {
     using G = SepTile<R, TH, CX>;
     constexpr int TW = G::TW, RA = G::RA, LW = G::LW, NR = G::NR;
     __shared__ __attribute__((aligned(16))) float lds[G::LDS_FLOATS];
@@ -179,8 +174,8 @@ __global__ __launch_bounds__(256) void sep_pers(const void* __restrict__ src, si
     if (t < 0) return;
     int x0, y0;
     tile_origin(t, tiles_x, TW, TH, x0, y0);
-    st.load(src, sp, W, H, x0 - RA, y0 - R, vec_ok, bd);
-    st.store(in_s);
+    st.load(src, sp, W, H, x0 - RA, y0 - R);
+    st.store(in_s, W, H, bd);
     __syncthreads();
     // Pipeline per tile: issue the next tile's loads, run the row pass, then (after the
     // barrier that frees in_s) move the prefetched registers into in_s BEFORE this tile's
@@ -190,12 +185,12 @@ __global__ __launch_bounds__(256) void sep_pers(const void* __restrict__ src, si
         if (tn >= 0) {
             int nx0, ny0;
             tile_origin(tn, tiles_x, TW, TH, nx0, ny0);
-            st.load(src, sp, W, H, nx0 - RA, ny0 - R, vec_ok, bd);
+            st.load(src, sp, W, H, nx0 - RA, ny0 - R);
         }
         sep_row_pass<R, TH, CX>(in_s, t_s, tx);
         __syncthreads();
-        if (tn >= 0) st.store(in_s);
-        sep_col_pass<T, R, TH, CX>(t_s, dst, dp, W, H, ty, x0, y0, vec_out);
+        if (tn >= 0) st.store(in_s, W, H, bd);
+        sep_col_pass<T, R, TH, CX>(t_s, dst, dp, W, H, ty, x0, y0);
         __syncthreads();
         t = tn;
         if (t >= 0) tile_origin(t, tiles_x, TW, TH, x0, y0);
@@ -207,13 +202,9 @@ hipError_t launch_pers_TR(const SepArgs& a) {
     using G = SepTile<R, TH, CX>;
     const int tiles_x = (a.W + G::TW - 1) / G::TW;
     const int tiles_y = (a.H + TH - 1) / TH;
-    const size_t al = 4 * (size_t)T::size;
-    const int vec_ok = ((uintptr_t)a.src % al == 0) && (a.sp % al == 0);
-    const int vec_out = ((uintptr_t)a.dst % al == 0) && (a.dp % al == 0);
     const void* k = reinterpret_cast<const void*>(&sep_pers<T, R, TH, CX>);
     hipLaunchKernelGGL((sep_pers<T, R, TH, CX>), dim3(persistent_grid(k, 256, tiles_x * tiles_y)), dim3(256), 0,
-                       a.st, a.src, a.sp, a.dst, a.dp, a.W, a.H, a.tx, a.ty, tiles_x, tiles_y, vec_ok, vec_out,
-                       a.bd);
+                       a.st, a.src, a.sp, a.dst, a.dp, a.W, a.H, a.tx, a.ty, tiles_x, tiles_y, a.bd);
     return hipGetLastError();
 }
 
@@ -326,8 +317,7 @@ __device__ __forceinline__ void stage_rows_img4(const void* __restrict__ src, si
 template <class T, int R, int TH, int CX, bool X4>
 __global__ __launch_bounds__(256) void sep_fused_img(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                      size_t dp, int W, int H, const float* __restrict__ tx,
-                                                     const float* __restrict__ ty, int tiles_x, int vec_in, int vec_out,
-                                                     Border bd) {
+                                                     const float* __restrict__ ty, int tiles_x, int vec_in, Border bd) {
     using G = SepTile<R, TH, CX>;
     __shared__ __attribute__((aligned(16))) float lds[G::LDS_FLOATS];
     float* in_s = lds;
@@ -340,7 +330,7 @@ __global__ __launch_bounds__(256) void sep_fused_img(const void* __restrict__ sr
     __syncthreads();
     sep_row_pass<R, TH, CX>(in_s, t_s, tx);
     __syncthreads();
-    sep_col_pass<T, R, TH, CX>(t_s, dst, dp, W, H, ty, x0, y0, vec_out != 0);
+    sep_col_pass<T, R, TH, CX>(t_s, dst, dp, W, H, ty, x0, y0);
 }
 
 template <class T, int R, int TH, int CX, bool X4>
@@ -349,10 +339,9 @@ hipError_t launch_img_TR(const SepArgs& a) {
     const int tiles_x = (a.W + G::TW - 1) / G::TW;
     const int tiles_y = (a.H + TH - 1) / TH;
     const size_t al = 4 * (size_t)T::size;
-    const int vec_out = ((uintptr_t)a.dst % al == 0) && (a.dp % al == 0);
     const int vec_in = ((uintptr_t)a.src % al == 0) && (a.sp % al == 0) && (T::size == 4 || a.W % 2 == 0);
     hipLaunchKernelGGL((sep_fused_img<T, R, TH, CX, X4>), dim3(tiles_x * tiles_y), dim3(256), 0, a.st, a.src, a.sp,
-                       a.dst, a.dp, a.W, a.H, a.tx, a.ty, tiles_x, vec_in, vec_out, a.bd);
+                       a.dst, a.dp, a.W, a.H, a.tx, a.ty, tiles_x, vec_in, a.bd);
     return hipGetLastError();
 }
 
@@ -410,7 +399,6 @@ hipError_t launch_colwalk_TR(const SepArgs& a) {
     d.src = a.src; d.dst = a.dst; d.sp = a.sp; d.dp = a.dp; d.tx = a.tx; d.ty = a.ty;
     d.W = a.W; d.H = a.H; d.r = R;
     d.vec_ok = ((uintptr_t)a.src % al == 0) && (a.sp % al == 0);
-    d.vec_out = ((uintptr_t)a.dst % al == 0) && (a.dp % al == 0);
     d.src_bytes = (unsigned)((size_t)(a.H - 1) * a.sp + (size_t)a.W * T::size);
     const int nstrips = (a.W + 63) / 64, nsegs = (a.H + SEG - 1) / SEG;
     const void* k = reinterpret_cast<const void*>(&sep_colwalk<T, R, SEG>);
@@ -455,23 +443,18 @@ bool supports_colwalk(const SepArgs& a) {
 template <class T, int R, int TH>
 __global__ __launch_bounds__(64) void sep_strip(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                 size_t dp, int W, int H, const float* __restrict__ tx,
-                                                const float* __restrict__ ty, int nstrips, int vec_in, int vec_out,
-                                                Border bd) {
+                                                const float* __restrict__ ty, int nstrips, Border bd) {
     const int strip = (int)(blockIdx.x % (unsigned)nstrips);
     const int y0 = (int)(blockIdx.x / (unsigned)nstrips) * TH;
-    sep_strip_body<T, R, TH>(src, sp, dst, dp, W, H, tx, ty, strip * StripGeom<R>::SW, y0, vec_in != 0,
-                             vec_out != 0, bd);
+    sep_strip_body<T, R, TH>(src, sp, dst, dp, W, H, tx, ty, strip * StripGeom<R>::SW, y0, bd);
 }
 
 template <class T, int R, int TH>
 hipError_t launch_strip_TR(const SepArgs& a) {
     const int nstrips = (a.W + StripGeom<R>::SW - 1) / StripGeom<R>::SW;
     const int rows = (a.H + TH - 1) / TH;
-    const size_t al = 4 * (size_t)T::size;
-    const int vec_in = ((uintptr_t)a.src % al == 0) && (a.sp % al == 0);
-    const int vec_out = ((uintptr_t)a.dst % al == 0) && (a.dp % al == 0);
     hipLaunchKernelGGL((sep_strip<T, R, TH>), dim3((unsigned)(nstrips * rows)), dim3(64), 0, a.st, a.src, a.sp, a.dst,
-                       a.dp, a.W, a.H, a.tx, a.ty, nstrips, vec_in, vec_out, a.bd);
+                       a.dp, a.W, a.H, a.tx, a.ty, nstrips, a.bd);
     return hipGetLastError();
 }
 

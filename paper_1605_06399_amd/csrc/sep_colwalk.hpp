@@ -20,7 +20,7 @@ struct DevImage {
     unsigned long long sp, dp;
     const float* tx;
     const float* ty;
-    int W, H, r, vec_ok, vec_out;
+    int W, H, r, vec_ok;
     unsigned src_bytes;   // extent of the source rows in bytes (the column walk's buffer size; 0 if >= 2^31)
 };
 
@@ -124,7 +124,7 @@ __device__ __forceinline__ DevImage uni(const DevImage& d) {
     u.sp = (unsigned long long)uni((int)d.sp) & 0xffffffffull;
     u.dp = ((unsigned long long)(unsigned)uni((int)(d.dp >> 32)) << 32) | (unsigned)uni((int)d.dp);
     u.tx = uni(d.tx); u.ty = uni(d.ty);
-    u.W = uni(d.W); u.H = uni(d.H); u.r = uni(d.r); u.vec_ok = uni(d.vec_ok); u.vec_out = uni(d.vec_out);
+    u.W = uni(d.W); u.H = uni(d.H); u.r = uni(d.r); u.vec_ok = uni(d.vec_ok);
     u.src_bytes = (unsigned)uni((int)d.src_bytes);
     return u;
 }
@@ -164,7 +164,7 @@ __device__ __forceinline__ void col_item(const DevImage& d, const ColItem& it, f
         if (s + 1 < nsteps) st.load(d, rs, it.x0, it.y0 + STEP * (s + 1) + R, inside);
         sep_row_pass<R, STEP - 2 * R, CX, 1>(in_s, t_s + 2 * R * CW, tx);
         __syncthreads();
-        sep_col_pass<T, R, STEP, CX, 6>(t_s, d.dst, d.dp, d.W, d.H, ty, it.x0, it.y0 + STEP * s, d.vec_out);
+        sep_col_pass<T, R, STEP, CX, 6>(t_s, d.dst, d.dp, d.W, d.H, ty, it.x0, it.y0 + STEP * s);
         __syncthreads();
     }
 }

@@ -72,18 +72,17 @@ __device__ __forceinline__ v4f strip_row_pass(const v4f v, const float* __restri
 }
 
 // One strip: output columns xs .. xs + SW - 1 (those below W) and rows y0 .. y0 + TH - 1
-// (those below H).  vec_in / vec_out: rows start 4-pixel aligned (16 B for float32).
+// (those below H).
 template <class T, int R, int TH>
 __device__ __forceinline__ void sep_strip_body(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                                size_t dp, int W, int H, const float* __restrict__ tx,
-                                               const float* __restrict__ ty, int xs, int y0, bool vec_in,
-                                               bool vec_out, Border bd = {}) {
+                                               const float* __restrict__ ty, int xs, int y0, Border bd = {}) {
     using G = StripGeom<R>;
     constexpr int D = G::D, U = G::U, Q = G::Q, HL = G::HL;
     constexpr int K = TH + 2 * R;   // input rows walked
     const int lane = threadIdx.x & 63;
     const int c = xs - G::RA + 4 * lane;
-    const bool inside = vec_in && c >= 0 && c + 4 <= W;
+    const bool inside = c >= 0 && c + 4 <= W;
     const int c0 = clampi(c, W), c1 = clampi(c + 1, W), c2 = clampi(c + 2, W), c3 = clampi(c + 3, W);
     // a column outside the image reads the constant (constant boundary) or its clamped pixel
     const bool o0 = bd.constant && (c < 0 || c >= W), o1 = bd.constant && (c + 1 < 0 || c + 1 >= W);
@@ -99,7 +98,7 @@ __device__ __forceinline__ void sep_strip_body(const void* __restrict__ src, siz
                    o3 ? bd.value : load_px<T>(src, row + (size_t)c3 * T::size));
     };
     const bool writer = lane >= HL && lane < 64 - HL && c < W;
-    const bool wvec = vec_out && c + 4 <= W;
+    const bool wvec = c + 4 <= W;
     v4f ring[U];
 #pragma unroll
     for (int i = 0; i < Q; ++i) ring[i] = i < K ? load_row(i) : mk4(0.f, 0.f, 0.f, 0.f);

@@ -1,6 +1,7 @@
 // Fused single-pass separable tile, shared by the per-image and batched kernels.
 #pragma once
 #include "icl_device.hpp"
+#include "tile_stage.hpp"
 
 namespace icl {
 
@@ -49,12 +50,12 @@ __device__ __forceinline__ void sep_row_pass(const float* __restrict__ in_s, flo
 
 // Column pass: lane owns 4 adjacent columns (group g of TW/4) and PYC consecutive rows;
 // the t_s rows it needs are read as float4, and the 4 outputs of a row are stored as one
-// vector when the destination rows are 4-pixel aligned (vec_out).
+// vector wherever they all lie in the image.
 // GROUP > 0 fences the schedule every GROUP staged rows, so that at most GROUP rows' reads are
 // in registers at a time (a kernel that must fit a register budget).
 template <class T, int R, int TH, int CX, int GROUP = 0>
 __device__ __forceinline__ void sep_col_pass(const float* __restrict__ t_s, void* __restrict__ dst, size_t dp, int W,
-                                             int H, const float* __restrict__ ty, int x0, int y0, bool vec_out) {
+                                             int H, const float* __restrict__ ty, int x0, int y0) {
     using G = SepTile<R, TH, CX>;
     constexpr int TW = G::TW, G4 = TW / 4, RPI = 256 / G4, PYC = TH / RPI;
     static_assert(PYC * RPI == TH, "tile rows must split evenly over the row groups");
@@ -86,7 +87,7 @@ __device__ __forceinline__ void sep_col_pass(const float* __restrict__ t_s, void
         if (y >= H) break;
         const size_t row = (size_t)y * dp;
         const v4f a = acc[py];
-        if (vec_out && x + 4 <= W) {
+        if (x + 4 <= W) {
             store4<T>(dst, row + (size_t)x * T::size, a);
         } else {
             if (x < W) store_px<T>(dst, row + (size_t)x * T::size, a.x);
@@ -98,53 +99,23 @@ __device__ __forceinline__ void sep_col_pass(const float* __restrict__ t_s, void
 }
 
 // Computes one TW x TH output tile whose top-left output pixel is (x0, y0), staging
-// directly (no prefetch).  `lds` holds SepTile::LDS_FLOATS floats.  vec: interior-in-x
-// tile with 4-pixel aligned rows, loaded with vector loads and no column clamps.
+// directly (no prefetch).  `lds` holds SepTile::LDS_FLOATS floats.
 template <class T, int R, int TH, int CX>
 __device__ __forceinline__ void sep_tile_body(const void* __restrict__ src, size_t sp, void* __restrict__ dst,
                                               size_t dp, int W, int H, const float* __restrict__ tx,
-                                              const float* __restrict__ ty, int x0, int y0, bool vec, bool vec_out,
-                                              float* __restrict__ lds, Border bd = {}) {
+                                              const float* __restrict__ ty, int x0, int y0, float* __restrict__ lds,
+                                              Border bd = {}) {
     using G = SepTile<R, TH, CX>;
     constexpr int RA = G::RA, LW = G::LW, NR = G::NR;
     float* in_s = lds;             // [NR][LW]
     float* t_s = lds + NR * LW;    // [NR][TW]
-    const int tid = threadIdx.x;
-    if (vec) {   // the tile's columns are inside the image: only rows can be outside
-        // every chunk's load is issued before any is written to LDS (a load-then-write loop
-        // would wait on each load in turn); rows outside the image load their clamped row and
-        // take the constant afterwards, so no branch separates the loads
-        constexpr int C4 = LW / 4, NCH = NR * C4, PER = (NCH + 255) / 256;
-        v4f v[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int idx = tid + 256 * i;
-            if (NCH % 256 != 0 && idx >= NCH) break;
-            const int rr = idx / C4, c4 = idx - rr * C4;
-            v[i] = load4<T>(src, (size_t)clampi(y0 - R + rr, H) * sp + (size_t)(x0 - RA + 4 * c4) * T::size);
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int idx = tid + 256 * i;
-            if (NCH % 256 != 0 && idx >= NCH) break;
-            const int rr = idx / C4, c4 = idx - rr * C4;
-            const int yy = y0 - R + rr;
-            if (bd.constant && (yy < 0 || yy >= H)) v[i] = mk4(bd.value, bd.value, bd.value, bd.value);
-            lds4(&in_s[rr * LW + 4 * c4], v[i]);
-        }
-    } else {
-        for (int idx = tid; idx < NR * LW; idx += 256) {
-            const int rr = idx / LW, c = idx - rr * LW;
-            const int yy = y0 - R + rr, xx = x0 - RA + c;
-            in_s[rr * LW + c] = (bd.constant && (yy < 0 || yy >= H || xx < 0 || xx >= W))
-                                    ? bd.value
-                                    : load_px<T>(src, (size_t)clampi(yy, H) * sp + (size_t)clampi(xx, W) * T::size);
-        }
-    }
+    Stage<T, NR, LW> st;           // every load is issued before any is written to LDS
+    st.load(src, sp, W, H, x0 - RA, y0 - R);
+    st.store(in_s, W, H, bd);
     __syncthreads();
     sep_row_pass<R, TH, CX>(in_s, t_s, tx);
     __syncthreads();
-    sep_col_pass<T, R, TH, CX>(t_s, dst, dp, W, H, ty, x0, y0, vec_out);
+    sep_col_pass<T, R, TH, CX>(t_s, dst, dp, W, H, ty, x0, y0);
 }
 
 }  // namespace icl

@@ -5,7 +5,7 @@
 // memory into registers (float4 per slot, 256 lanes), so the loads of the NEXT
 // tile can be in flight while the current one is computed from LDS, and then
 // writes the registers to LDS.  Reads outside the image follow the boundary: clamp or a
-// constant (Border), or zero with ZERO_PAD.
+// constant (Border).
 #pragma once
 #include <type_traits>
 
@@ -13,47 +13,48 @@
 
 namespace icl {
 
-template <class T, int NR, int LW, bool ZERO_PAD = false>
+// Columns x .. x + 3 of a row (x a multiple of 4, on either side of the row's ends too) read through the
+// clamp, in two parts that need no branch: a vector load from the nearest position inside the row, then
+// its elements moved to where they belong.  Rows of fewer than 4 pixels are read pixel by pixel.
+template <class T>
+__device__ __forceinline__ v4f load4_clamped(const void* __restrict__ src, size_t row, int W, int x) {
+    if (W >= 4) return load4<T>(src, row + (size_t)min(max(x, 0), W - 4) * T::size);
+    v4f v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = load_px<T>(src, row + (size_t)clampi(x + q, W) * T::size);
+    return v;
+}
+__device__ __forceinline__ v4f fix4_clamped(v4f v, int W, int x) {
+    if (W < 4) return v;
+    const int d = x - min(max(x, 0), W - 4);   // right of the row's end: element q is the loaded q + d, at most the last
+    if (d >= 4 || (d & 2 && d > 0)) v = mk4(v.z, v.w, v.w, v.w);
+    if (d >= 4 || (d & 1 && d > 0)) v = mk4(v.y, v.z, v.w, v.w);
+    if (d < 0) v = mk4(v.x, v.x, v.x, v.x);    // left of column 0: d <= -4
+    return v;
+}
+// The elements of columns x .. x + 3 of row y that lie outside the image replaced by c.
+__device__ __forceinline__ v4f outside4(v4f v, int W, int H, int x, int y, float c) {
+    const bool row = y < 0 || y >= H;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (row || x + q < 0 || x + q >= W) v[q] = c;
+    return v;
+}
+
+template <class T, int NR, int LW>
 struct Stage {
     static constexpr int C4 = LW / 4;
     static constexpr int N = (NR * C4 + 255) / 256;
     v4f v[N];
+    int gx = 0, gy = 0;   // top-left pixel of the loaded tile (gx = -1: a constant fill)
 
-    // One float4 chunk of staged row data starting at pixel x of a row.  With `aligned`
-    // rows (4-pixel aligned base and pitch, x a multiple of 4) a chunk is either fully
-    // inside the row (one vector load), fully outside (zeros, or the clamped edge pixel
-    // broadcast), or straddles the right edge (per element; only when W % 4 != 0).
-    // bd: the boundary of the convolution kernels (clamp or a constant); ZERO_PAD, the
-    // adjoint's zero extension, takes precedence.
-    __device__ __forceinline__ static v4f chunk(const void* __restrict__ src, size_t row, int W, int x, bool aligned,
-                                                Border bd = {}) {
-        if (aligned && x >= 0 && x + 4 <= W) return load4<T>(src, row + (size_t)x * T::size);
-        if (aligned && (x + 4 <= 0 || x >= W)) {
-            if (ZERO_PAD) return mk4(0.f, 0.f, 0.f, 0.f);
-            if (bd.constant) return mk4(bd.value, bd.value, bd.value, bd.value);
-            const float e = load_px<T>(src, row + (size_t)clampi(x, W) * T::size);
-            return mk4(e, e, e, e);
-        }
-        float e[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int xx = x + q;
-            const bool out = xx < 0 || xx >= W;
-            e[q] = (ZERO_PAD && out) ? 0.f
-                   : (bd.constant && out) ? bd.value
-                                          : load_px<T>(src, row + (size_t)clampi(xx, W) * T::size);
-        }
-        return mk4(e[0], e[1], e[2], e[3]);
-    }
-
-    // Load the tile with top-left pixel (gx0, gy0); gx0 must be a multiple of 4 when
-    // `aligned` (rows 4-pixel aligned in memory).
-    __device__ __forceinline__ void load(const void* __restrict__ src, size_t sp, int W, int H, int gx0, int gy0,
-                                         bool aligned, Border bd = {}) {
-        // A tile that lies inside the image (the work-group's usual case) takes straight vector
-        // loads: no branch between them, so they are all in flight together.  The general path
-        // below branches per chunk, and the compiler then waits on each chunk's loads.
-        if (aligned && gx0 >= 0 && gx0 + LW <= W && gy0 >= 0 && gy0 + NR <= H) {
+    // Load the tile with top-left pixel (gx0, gy0), gx0 a multiple of 4.  Only loads: nothing here waits
+    // for one, so a tile can be in flight while another is computed.
+    __device__ __forceinline__ void load(const void* __restrict__ src, size_t sp, int W, int H, int gx0, int gy0) {
+        gx = gx0;
+        gy = gy0;
+        // A tile that lies inside the image (the work-group's usual case) takes straight vector loads.
+        if (inside(W, H)) {
 #pragma unroll
             for (int k = 0; k < N; ++k) {
                 const int idx = (int)threadIdx.x + 256 * k;
@@ -63,38 +64,45 @@ struct Stage {
             }
             return;
         }
+        // A tile at the image's edge does the same from clamped addresses, and store() puts the pixels in
+        // their places (a branch per chunk would make the compiler wait on each load in turn: 57 against
+        // 44 us on a 256^3 volume, half of whose 64-column tiles are at an edge).
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             const int idx = (int)threadIdx.x + 256 * k;
             if (N * 256 != NR * C4 && idx >= NR * C4) break;
             const int rr = idx / C4, c4 = idx - rr * C4;
-            const int yy = gy0 + rr;
-            if (ZERO_PAD && (yy < 0 || yy >= H)) {
-                v[k] = mk4(0.f, 0.f, 0.f, 0.f);
-                continue;
-            }
-            if (bd.constant && (yy < 0 || yy >= H)) {
-                v[k] = mk4(bd.value, bd.value, bd.value, bd.value);
-                continue;
-            }
-            v[k] = chunk(src, (size_t)clampi(yy, H) * sp, W, gx0 + 4 * c4, aligned, bd);
+            v[k] = load4_clamped<T>(src, (size_t)clampi(gy0 + rr, H) * sp, W, gx0 + 4 * c4);
         }
     }
 
-    // Every element the constant c (a whole staged region outside the image).
+    // Every element the constant c (a whole staged region outside the image): stored as it is.
     __device__ __forceinline__ void fill(float c) {
 #pragma unroll
         for (int k = 0; k < N; ++k) v[k] = mk4(c, c, c, c);
+        gx = -1;
     }
 
-    __device__ __forceinline__ void store(float* __restrict__ s) const {
+    // Write the loaded tile to LDS.  bd: the boundary (clamp or a constant).
+    __device__ __forceinline__ void store(float* __restrict__ s, int W, int H, Border bd = {}) const {
+        const bool edge = gx != -1 && !inside(W, H);
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             const int idx = (int)threadIdx.x + 256 * k;
             if (N * 256 != NR * C4 && idx >= NR * C4) break;
             const int rr = idx / C4, c4 = idx - rr * C4;
-            lds4(&s[rr * LW + 4 * c4], v[k]);
+            v4f e = v[k];
+            if (edge) {
+                const int x = gx + 4 * c4, y = gy + rr;
+                e = fix4_clamped(e, W, x);
+                if (bd.constant) e = outside4(e, W, H, x, y, bd.value);
+            }
+            lds4(&s[rr * LW + 4 * c4], e);
         }
+    }
+
+    __device__ __forceinline__ bool inside(int W, int H) const {
+        return gx >= 0 && gx + LW <= W && gy >= 0 && gy + NR <= H;
     }
 };
 
@@ -183,7 +191,12 @@ struct RStage {
         for (int k = 0; k < K; ++k) {
             const int rr = ry + 8 * k;
             if (rr >= NR) break;
-            v[k] = Stage<T, 1, 4>::chunk(src, (size_t)clampi(gy0 + rr, H) * sp, W, x, vec);
+            v[k] = load4_clamped<T>(src, (size_t)clampi(gy0 + rr, H) * sp, W, x);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (ry + 8 * k >= NR) break;
+            v[k] = fix4_clamped(v[k], W, x);
         }
     }
 
