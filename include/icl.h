@@ -435,7 +435,8 @@ icl_math icl_get_math(void);
 /* Arithmetic a variant computes in (static string, NULL if out of range):
  *   "fp32_valu"   float32 vector FMA          "fp32_mfma"  float32 matrix instructions
  *   "fp16x3_mfma" float16 hi/lo split on the matrix cores (see ICL_MATH_F16_SPLIT)
- *   "int32_valu"  exact integer arithmetic (icl_conv2d_u8) */
+ *   "int32_valu"  exact integer arithmetic (icl_conv2d_u8): 32-bit, or bytes on the matrix cores with
+ *                 32-bit accumulation ("mfma_i8") */
 const char* icl_variant_arith(icl_op op, int index);
 
 icl_status icl_tune_save(const char* path);
@@ -459,7 +460,9 @@ const char* icl_variant_name(icl_op op, int index);     /* NULL if out of range 
  * on or off.  A forced variant that cannot run a call (radius not compiled,
  * missing workspace) makes that call return ICL_ERR_UNSUPPORTED / ICL_ERR_WORKSPACE. */
 icl_status icl_force_variant(icl_op op, int index);
-/* Variant the next call with these parameters would launch (host out). */
+/* Variant the next call with these parameters would launch (host out).  For ICL_OP_CONV2D_U8 with a radius
+ * above 4 the table holds the plain kernel alone (index 0): unforced calls run the matrix-core walk of
+ * "mfma_i8" there, with the same bytes. */
 icl_status icl_selected_variant(icl_op op, icl_dtype dtype, int radius, int width, int height,
                                 int* index);
 

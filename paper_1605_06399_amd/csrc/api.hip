@@ -403,8 +403,11 @@ icl_status icl_conv2d_u8(const uint8_t* src, size_t src_pitch, uint8_t* dst, siz
     int count;
     const Variant<U8Args>* tab = conv2d_u8_variants(&count);
     const int deflt = conv2d_u8_default(a);
-    return dispatch(ICL_OP_CONV2D_U8, tab, count, a,
-                    select_variant(ICL_OP_CONV2D_U8, ICL_U8, radius, width, height, deflt, a.st), deflt);
+    const int v = select_variant(ICL_OP_CONV2D_U8, ICL_U8, radius, width, height, deflt, a.st);
+    // above the strips' radius the table holds the plain kernel alone: unforced calls take the matrix-core walk
+    if (v == 0 && deflt == 0 && !variant_forced(ICL_OP_CONV2D_U8) && supports_conv2d_u8_mfma(a))
+        return hip_status(launch_conv2d_u8_mfma(a));
+    return dispatch(ICL_OP_CONV2D_U8, tab, count, a, v, deflt);
 }
 
 icl_status icl_harris(const float* src, size_t src_pitch, float* resp, size_t resp_pitch, int width, int height,

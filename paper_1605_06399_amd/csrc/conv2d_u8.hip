@@ -285,6 +285,12 @@ hipError_t launch_strip(const U8Args& a) {
 
 bool supports_strip(const U8Args& a) { return a.r >= 0 && a.r <= U8_STRIP_MAX_R; }
 
+// The matrix-core walk as a table entry: radius 1 .. 4 (the range of the strips; a radius of 0 and rows
+// under 16 pixels run the strips).
+hipError_t launch_mfma(const U8Args& a) {
+    return a.r >= 1 && supports_conv2d_u8_mfma(a) ? launch_conv2d_u8_mfma(a) : launch_strip<16, 4>(a);
+}
+
 const Variant<U8Args> kConv2dU8[] = {
     {"plain", supports_plain, launch_plain},
     {"strip_p4_t16", supports_strip, launch_strip<16, 4>},
@@ -294,6 +300,7 @@ const Variant<U8Args> kConv2dU8[] = {
     {"strip_p4_t24", supports_strip, launch_strip<24, 4>},
     {"strip_p4_t16_q16", supports_strip, launch_strip<16, 4, 16>},
     {"strip_p4_t12_q16", supports_strip, launch_strip<12, 4, 16>},
+    {"mfma_i8", supports_strip, launch_mfma},
 };
 
 }  // namespace
@@ -303,6 +310,8 @@ const Variant<U8Args>* conv2d_u8_variants(int* count) {
     return kConv2dU8;
 }
 
-int conv2d_u8_default(const U8Args& a) { return supports_strip(a) ? 1 : 0; }
+// mfma_i8 for radius 1 .. 4, the strips for 0; wider windows are plain in the table, and the entry point runs
+// the matrix-core walk for them
+int conv2d_u8_default(const U8Args& a) { return !supports_strip(a) ? 0 : a.r >= 1 ? 8 : 1; }
 
 }  // namespace icl

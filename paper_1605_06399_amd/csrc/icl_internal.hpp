@@ -131,6 +131,8 @@ int conv2d_default(const Conv2dArgs&);
 bool supports_conv2d_mfma(const Conv2dArgs&);       // the matrix-core variant (conv2d_mfma.hip)
 hipError_t launch_conv2d_mfma(const Conv2dArgs&);
 int conv2d_u8_default(const U8Args&);
+bool supports_conv2d_u8_mfma(const U8Args&);       // the matrix-core walk, radius 1..7 (conv2d_u8_mfma.hip)
+hipError_t launch_conv2d_u8_mfma(const U8Args&);
 int harris_default(const HarrisArgs&);
 int nms_default(const NmsArgs&);
 int corners_default(const CornersArgs&);
