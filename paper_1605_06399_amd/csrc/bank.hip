@@ -1034,6 +1034,134 @@ hipError_t bwd_wm_RT(const BankArgs& a) {
     return hipGetLastError();
 }
 
+// The same product for problems of few tiles: tiles of 64 columns x 16 rows (four rows per wave) walked by a
+// grid of `parts` work-groups, one partial each.  A 64 x 256 tile per work-group leaves most of the chip idle
+// up to some hundreds of tiles, and its four staged sub-tiles run one after another: 4 x 8 x 201 x 200, r = 2
+// is 16 of them and took 95 us; here 208 tiles on 112 work-groups take 22 (16 x 16 x 512^2, r = 4, 256 of
+// them: 160 and 125 us).  The number of work-groups is bounded by the partials that the workspace is sized for.  Taps on the matrix cores and, where one is alone in its 16-tap block, the tail
+// as above; the steps take pixel-strided pixels (16 q + st).
+constexpr int GWS_H = 16;
+
+template <int R>
+__global__ __launch_bounds__(256, 4) void bank_bwd_ws_k(const float* __restrict__ gy, const float* __restrict__ x,
+                                                     float* __restrict__ part, int F, int H, int W, int tiles_x,
+                                                     int tiles_img, int ntiles, int parts) {
+    constexpr int N = 2 * R + 1, NK = N * N, NT = (NK + 15) / 16;
+    constexpr bool TV = NK % 16 == 1;
+    constexpr int NTM = TV ? NT - 1 : NT;
+    constexpr int RA = (R + 3) & ~3, LWS = GWM_T + 2 * RA, LW = LWS + 8, NR = GWS_H + 2 * R;
+    constexpr int C4 = LWS / 4, NCH = NR * C4, PER = (NCH + 255) / 256;
+    constexpr int S_FLOATS = NR * LW, RED_FLOATS = 4 * 16 * NT * 16;
+    __shared__ __attribute__((aligned(16))) float s[S_FLOATS > RED_FLOATS ? S_FLOATS : RED_FLOATS];
+    auto red = reinterpret_cast<float (*)[16][NT * 16]>(s);
+    const size_t hw = (size_t)H * W;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, fl = lane & 15, q = lane >> 4;
+    const bool frow = fl < F;
+    int off[NT];   // LDS offset of this lane's tap (clamped into range for the padding columns)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int k = min(16 * t + fl, NK - 1);
+        off[t] = (k / N) * LW + (k % N) + RA - R;
+    }
+    constexpr int OFFL = ((NK - 1) / N) * LW + (NK - 1) % N + RA - R;   // the last tap's LDS offset
+    v4f acc[NTM];
+#pragma unroll
+    for (int t = 0; t < NTM; ++t) acc[t] = mk4(0.f, 0.f, 0.f, 0.f);
+    float accl = 0.f;
+    for (int tile = (int)blockIdx.x; tile < ntiles; tile += parts) {
+        const int n = tile / tiles_img, ti = tile - n * tiles_img;
+        int x0, y0;
+        tile_origin(ti, tiles_x, GWM_T, GWS_H, x0, y0);
+        const float* xp = x + (size_t)n * hw;
+        const float* g = gy + ((size_t)n * F + (frow ? fl : 0)) * hw;
+        // the wave's four rows of gy: lane (filter, q) takes pixels 16 q .. 16 q + 15; outside the image and
+        // past the last filter 0
+        const int xb = x0 + 16 * q;
+        float ga[GWS_H / 4][16];
+#pragma unroll
+        for (int row = 0; row < GWS_H / 4; ++row) {
+            const int yy = y0 + wave * (GWS_H / 4) + row;
+            const float* grow = g + (size_t)min(yy, H - 1) * W;
+            const bool live = frow && yy < H;
+            if (xb + 16 <= W) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const v4f v = load4<F32>(grow, (size_t)(xb + 4 * m) * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ga[row][4 * m + e] = live ? v[e] : 0.f;
+                }
+            } else {
+#pragma unroll
+                for (int st = 0; st < 16; ++st) {
+                    const float v = grow[min(xb + st, W - 1)];
+                    ga[row][st] = (live && xb + st < W) ? v : 0.f;
+                }
+            }
+        }
+        // x tile with its halo, clamped
+        v4f v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int idx = (int)threadIdx.x + 256 * i;
+            if (NCH % 256 != 0 && idx >= NCH) break;
+            const int rr = idx / C4, c4 = idx - rr * C4;
+            v[i] = load4_clamped<F32>(xp, (size_t)clampi(y0 - R + rr, H) * W * 4, W, x0 - RA + 4 * c4);
+        }
+        __syncthreads();   // the previous tile's products are done with s
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int idx = (int)threadIdx.x + 256 * i;
+            if (NCH % 256 != 0 && idx >= NCH) break;
+            const int rr = idx / C4, c4 = idx - rr * C4;
+            lds4(&s[rr * LW + 4 * c4], fix4_clamped(v[i], W, x0 - RA + 4 * c4));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int row = 0; row < GWS_H / 4; ++row) {
+            const int py = wave * (GWS_H / 4) + row;
+#pragma unroll
+            for (int st = 0; st < 16; ++st) {
+                const int base = py * LW + 16 * q + st;
+#pragma unroll
+                for (int t = 0; t < NTM; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[row][st], s[base + off[t]], acc[t], 0, 0, 0);
+                if constexpr (TV) accl = fmaf(ga[row][st], s[base + OFFL], accl);
+            }
+        }
+    }
+    if constexpr (TV) {   // lane (filter fl, pixel group q): add the four pixel groups
+        accl += __shfl_xor(accl, 16, 64);
+        accl += __shfl_xor(accl, 32, 64);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NTM; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave][4 * q + i][16 * t + fl] = acc[t][i];
+    if constexpr (TV)
+        if (q == 0) red[wave][fl][NK - 1] = accl;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * NK; e += 256) {
+        const int f = e / NK, k = e - f * NK;
+        if (f >= F) continue;
+        const float sum = ((red[0][f][k] + red[1][f][k]) + red[2][f][k]) + red[3][f][k];
+        part[((size_t)f * NK + k) * parts + blockIdx.x] = sum;
+    }
+}
+
+template <int R>
+hipError_t bwd_ws_R(const BankArgs& a) {
+    const int tx = (a.w + GWM_T - 1) / GWM_T, ty = (a.h + GWS_H - 1) / GWS_H;
+    const int ntiles = a.n * tx * ty, nk = (2 * R + 1) * (2 * R + 1);
+    const size_t most = bank_bwd_filter_workspace(a.n, a.f, a.h, a.w, R) / ((size_t)a.f * nk * sizeof(float));
+    const int parts = (int)std::min<size_t>({(size_t)ntiles, most, (size_t)1024});
+    float* part = static_cast<float*>(a.ws);
+    hipLaunchKernelGGL(bank_bwd_ws_k<R>, dim3((unsigned)parts), dim3(256), 0, a.st, a.a, a.b, part, a.f, a.h, a.w, tx,
+                       tx * ty, ntiles, parts);
+    hipLaunchKernelGGL(bank_bwd_w2_k, dim3((unsigned)(a.f * nk)), dim3(256), 0, a.st, part, a.out, parts, a.scale);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ launchers
 int bank_vec(const float* a, const float* b, int W) {
     return ((uintptr_t)a % 16 == 0) && ((uintptr_t)b % 16 == 0) && (W % 4 == 0);
@@ -1145,6 +1273,7 @@ hipError_t bwd_wmp4_R(const BankArgs& a) { return bwd_wm_RT<R, 4, true>(a); }
 template <int R>
 hipError_t bwd_wmpt4_R(const BankArgs& a) { return bwd_wm_RT<R, 4, true, true>(a); }
 
+hipError_t launch_bwd_ws(const BankArgs& a) { ICL_BANK_SWITCH(bwd_ws_R) }
 hipError_t launch_bwd_w4(const BankArgs& a) { ICL_BANK_SWITCH(bwd_w4_R) }
 hipError_t launch_bwd_wm(const BankArgs& a) { ICL_BANK_SWITCH(bwd_wm_R) }
 hipError_t launch_bwd_wm4(const BankArgs& a) { ICL_BANK_SWITCH(bwd_wm4_R) }
@@ -1172,7 +1301,8 @@ const Variant<BankArgs> kBwdW[] = {{"wave_t32x64", supports_bwd_w, launch_bwd_w}
                                    {"mfma_t64x256", supports_bwd_wm, launch_bwd_wm4},
                                    {"mfma_px_t64", supports_bwd_wm, launch_bwd_wmp},
                                    {"mfma_px_t64x256", supports_bwd_wm, launch_bwd_wmp4},
-                                   {"mfma_px_tail_t64x256", supports_bwd_wm, launch_bwd_wmpt4}};
+                                   {"mfma_px_tail_t64x256", supports_bwd_wm, launch_bwd_wmpt4},
+                                   {"mfma_walk_t64x16", supports_bwd_wm, launch_bwd_ws}};
 
 // ------------------------------------------------------------------ forward on the matrix cores
 // y[f][p] = sum_k w[f][k] x[p + off(k)]: filters as rows, pixels as columns, taps as the
@@ -1594,7 +1724,13 @@ const Variant<BankArgs>* bank_bwd_filter_variants(int* count) {
 
 int bank_fwd_default(const BankArgs& a) { return supports_mfma16(a) ? 4 : supports_pers(a) ? 2 : 1; }   // mfma_px_t64
 int bank_bwd_input_default(const BankArgs& a) { return supports_pers(a) ? 2 : 1; }
-int bank_bwd_filter_default(const BankArgs& a) { return a.f <= 16 ? 7 : 2; }   // mfma_px_tail_t64x256, else block4_t64x256
+// mfma_walk_t64x16 where the 64 x 256 tiles are fewer than two per CU, else mfma_px_tail_t64x256 (16 x 512^2
+// pixels are 256 tiles: 125 against 160 us at r = 4; 8 x 1024^2 are 512: 245 against 236); block4_t64x256 above
+// 16 filters
+int bank_bwd_filter_default(const BankArgs& a) {
+    const long long tiles = (long long)a.n * ((a.w + 63) / 64) * ((a.h + 255) / 256);
+    return a.f > 16 ? 2 : tiles < 512 ? 8 : 7;
+}
 const Variant<BankSseArgs>* bank_fwd_sse_variants(int* count) {
     *count = (int)(sizeof(kFwdSse) / sizeof(kFwdSse[0]));
     return kFwdSse;
