@@ -308,9 +308,24 @@ hipError_t launch_pers(const Conv2dArgs& a) {
     }
 }
 
+// The untuned choice (its table name is that of the 64 x 64 tile it was).  4096^2, us, 64 x 64 tiles as they
+// were / here: float32 r = 1 38 / 29, r = 3 45 / 36, r = 5 77 / 59, r = 7 120 / 87; bfloat16 r = 2 29 / 26, r = 5
+// 73 / 63.
+//  - persistent tiles keep the next tile's loads in flight under the FMAs.  64 x 32 of them: the smaller tile
+//    puts more work-groups on a small image (1921 x 1083 r = 5: 14 us; 64 x 64 20) and loses nothing on a large one
+//  - 128 x 64 for wide float32 windows on images of 8 Mpx and more (two such tiles per CU): a lane's 8 x 4 block
+//    reads fewer window elements per FMA (r = 7: 85 against 90 us)
+//  - half storage with narrow windows moves half the bytes and a tile's work no longer covers its loads'
+//    registers: single-shot 64 x 32 tiles (r = 1: 19 against 24 us)
+hipError_t launch_default(const Conv2dArgs& a) {
+    if (a.dt != ICL_F32 && a.r <= 2) return launch_lds<4, 2, 1>(a);
+    if (a.dt == ICL_F32 && a.r >= 5 && (size_t)a.W * a.H >= ((size_t)1 << 23)) return launch_pers<8, 4>(a);
+    return launch_pers<4, 2>(a);
+}
+
 const Variant<Conv2dArgs> kConv2d[] = {
     {"plain", supports_plain, launch_plain},
-    {"lds_p4x4_o0", supports_lds, launch_lds<4, 4, 0>},
+    {"lds_p4x4_o0", supports_lds, launch_default},
     {"lds_p4x4_o1", supports_lds, launch_lds<4, 4, 1>},
     {"lds_p4x8_o0", supports_lds, launch_lds<4, 8, 0>},
     {"lds_p4x2_o1", supports_lds, launch_lds<4, 2, 1>},
