@@ -19,15 +19,19 @@
 //                loaded once, the 3 x 3 neighbourhood from registers and DPP lane shifts;
 //                the border bands run through row4.  16-byte aligned response rows.
 //   stream_a_t{TH}: one wave per 256-column strip at a multiple of 256 and TH rows (r = 1):
-//                all 64 lanes own outputs, aligned 1 KiB row reads and 256-byte mask writes,
-//                the two outside columns as broadcast values; columns right of the last whole
-//                strip run through row4.  _sm: strip-major wave order.
+//                all 64 lanes own outputs, 1 KiB row reads and 256-byte mask writes, the two
+//                outside columns as broadcast values; the last strip of another width ends at
+//                the last column.  _sm: strip-major wave order.
+//   strips_any_t8: the stream_a strips of 8 rows for rows of any alignment, row4 below 256
+//                columns, plain for wider windows (the default for r = 1).
 #include "harris_strip.hpp"
 #include "icl_device.hpp"
 #include "icl_internal.hpp"
 
 namespace icl {
 namespace {
+
+typedef uint32_t u32_any __attribute__((aligned(1)));   // four mask bytes at any address
 
 __global__ __launch_bounds__(256) void nms_plain(const float* __restrict__ R, size_t rp, uint8_t* __restrict__ M,
                                                  size_t mp, int W, int H, int r, float tau) {
@@ -56,7 +60,7 @@ bool supports_plain(const NmsArgs& a) { return a.r >= 1 && a.r <= ICL_MAX_NMS_RA
 // ------------------------------------------------------------------ four pixels per lane, r = 1
 __device__ __forceinline__ void row6(const float* __restrict__ row, int x, int W, bool interior, float v[6]) {
     if (interior) {
-        const v4f m = *reinterpret_cast<const v4f*>(row + x);
+        const v4f m = *reinterpret_cast<const v4f_any*>(row + x);
         v[0] = row[x - 1]; v[1] = m.x; v[2] = m.y; v[3] = m.z; v[4] = m.w; v[5] = row[x + 4];
     } else {
 #pragma unroll
@@ -68,14 +72,14 @@ __device__ __forceinline__ void row6(const float* __restrict__ row, int x, int W
 // below xl, the rest start at xr and write columns below W (the whole image: n0 = all, xl = W).
 __global__ __launch_bounds__(256) void nms_row4(const float* __restrict__ R, size_t rp, uint8_t* __restrict__ M,
                                                 size_t mp, int W, int H, float tau, int groups_x, int n0, int xl,
-                                                int xr, int vec_ok) {
+                                                int xr) {
     const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
     const int y = (int)(gid / groups_x);
     const int gx = (int)(gid - (long long)y * groups_x);
     const int x = gx < n0 ? 4 * gx : xr + 4 * (gx - n0);
     const int xe = gx < n0 ? xl : W;
     if (y >= H) return;
-    const bool interior = vec_ok && x >= 1 && x + 5 <= W;
+    const bool interior = x >= 1 && x + 5 <= W;
     float a[6], b[6], c[6];
     const char* base = reinterpret_cast<const char*>(R);
     row6(reinterpret_cast<const float*>(base + (size_t)clampi(y - 1, H) * rp), x, W, interior, a);
@@ -90,8 +94,8 @@ __global__ __launch_bounds__(256) void nms_row4(const float* __restrict__ R, siz
         bits |= (keep ? 1u : 0u) << (8 * p);
     }
     uint8_t* out = M + (size_t)y * mp + x;
-    if (vec_ok && x + 4 <= xe) {
-        *reinterpret_cast<uint32_t*>(out) = bits;
+    if (x + 4 <= xe) {
+        *reinterpret_cast<u32_any*>(out) = bits;
     } else {
         for (int p = 0; p < 4 && x + p < xe; ++p) out[p] = (uint8_t)((bits >> (8 * p)) & 1u);
     }
@@ -103,9 +107,8 @@ hipError_t launch_row4_bands(const NmsArgs& a, int xl, int xr) {
     const int n1 = xl >= a.W ? 0 : (a.W - xr + 3) / 4;
     const int groups_x = n0 + n1;
     const long long n = (long long)groups_x * a.H;
-    const int vec_ok = ((uintptr_t)a.R % 16 == 0) && (a.rp % 16 == 0) && ((uintptr_t)a.M % 4 == 0) && (a.mp % 4 == 0);
     hipLaunchKernelGGL(nms_row4, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, a.st, a.R, a.rp, a.M, a.mp, a.W, a.H,
-                       a.tau, groups_x, n0, xl, xr, vec_ok);
+                       a.tau, groups_x, n0, xl, xr);
     return hipGetLastError();
 }
 
@@ -135,7 +138,7 @@ __global__ __launch_bounds__(256) void nms_stream(const float* __restrict__ R, s
     const int y0 = (wv / nstrips) * TH;
     const int c = NS_XL + strip * NS_COLS - 4 + 4 * lane;
     const char* col = reinterpret_cast<const char*>(R) + (size_t)c * 4;
-    auto row = [&](int y) { return *reinterpret_cast<const v4f*>(col + (size_t)y * rp); };
+    auto row = [&](int y) { return *reinterpret_cast<const v4f_any*>(col + (size_t)y * rp); };
     const bool writer = lane >= 1 && lane <= 62;
     uint8_t* out_col = M + c;
     if (y0 >= 1 && y0 + TH <= H - 1) {
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(256) void nms_stream(const float* __restrict__ R, s
             constexpr int m = decltype(m_c)::value;
             const uint32_t bits = nms_bits(ring[m % RING], ring[(m + 1) % RING], ring[(m + 2) % RING], tau);
             if constexpr (m + RING <= TH + 1) ring[m % RING] = row(ybase + m + RING);
-            if (writer) *reinterpret_cast<uint32_t*>(out_col + (size_t)(y0 + m) * mp) = bits;
+            if (writer) *reinterpret_cast<u32_any*>(out_col + (size_t)(y0 + m) * mp) = bits;
         });
         return;
     }
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(256) void nms_stream(const float* __restrict__ R, s
         const int y = y0 + m;
         if (y >= H) break;
         const uint32_t bits = nms_bits(row(clampi(y - 1, H)), row(y), row(clampi(y + 1, H)), tau);
-        if (writer) *reinterpret_cast<uint32_t*>(out_col + (size_t)y * mp) = bits;
+        if (writer) *reinterpret_cast<u32_any*>(out_col + (size_t)y * mp) = bits;
     }
 }
 
@@ -185,8 +188,9 @@ hipError_t launch_stream(const NmsArgs& a) {
 // four output columns, so each response row is one aligned 1 KiB read and each mask row one
 // aligned 256-byte write.  The two columns just outside the strip (its neighbours' edge
 // pixels, clamped at the image border) are read as one broadcast value each and replace the
-// DPP shift's missing neighbour in lanes 0 and 63.  Columns right of the last whole strip
-// run through the row kernel.
+// DPP shift's missing neighbour in lanes 0 and 63.  Bound by HBM (5 B/px); 8192^2 in 62 us = 5.4 TB/s.
+// The columns right of the last whole strip went through the row kernel as a second launch; now a
+// last strip ends at column W - 1 and drops what the one before it writes (1919 x 1081, r = 1: 10.8 -> 5 us).
 __device__ __forceinline__ uint32_t nms_bits_edges(v4f a, v4f b, v4f c, float al_e, float ar_e, float bl_e, float br_e,
                                                    float cl_e, float cr_e, float tau) {
     const float al = lane_from_left_or(a.w, al_e), ar = lane_from_right_or(a.x, ar_e);
@@ -227,12 +231,25 @@ __global__ __launch_bounds__(256) void nms_stream_a(const float* __restrict__ R,
         strip = wv % nstrips;
         y0 = (wv / nstrips) * TH;
     }
-    const int x0 = strip * 256;
+    // the last strip of a width that is no multiple of 256 ends at the image's last column and writes the columns
+    // that the strip before it leaves
+    const int x0 = min(strip * 256, W - 256);
     const int xl = x0 > 0 ? x0 - 1 : 0, xr = x0 + 256 < W ? x0 + 256 : W - 1;
     const char* base = reinterpret_cast<const char*>(R);
-    auto row = [&](int y) { return *reinterpret_cast<const v4f*>(base + (size_t)y * rp + (size_t)(x0 + 4 * lane) * 4); };
+    auto row = [&](int y) { return *reinterpret_cast<const v4f_any*>(base + (size_t)y * rp + (size_t)(x0 + 4 * lane) * 4); };
     auto px = [&](int y, int x) { return *reinterpret_cast<const float*>(base + (size_t)y * rp + (size_t)x * 4); };
     uint8_t* out = M + x0 + 4 * lane;
+    const int skip = strip * 256 - (x0 + 4 * lane);   // this lane's columns that are the previous strip's
+    auto put = [&](int y, uint32_t bits) {
+        uint8_t* o = out + (size_t)y * mp;
+        if (skip <= 0) {
+            *reinterpret_cast<u32_any*>(o) = bits;
+        } else {
+#pragma unroll
+            for (int q = 1; q < 4; ++q)
+                if (q >= skip) o[q] = (uint8_t)(bits >> (8 * q));
+        }
+    };
     if (y0 >= 1 && y0 + TH <= H - 1) {
         // interior: output row m reads rows y0 - 1 + m + {0, 1, 2} from a ring of RING rows
         // (row i of the block in slot i mod RING), each loaded RING - 2 rows before use; a
@@ -256,7 +273,7 @@ __global__ __launch_bounds__(256) void nms_stream_a(const float* __restrict__ R,
                 el[a] = px(ybase + m + RING, xl);
                 er[a] = px(ybase + m + RING, xr);
             }
-            *reinterpret_cast<uint32_t*>(out + (size_t)(y0 + m) * mp) = bits;
+            put(y0 + m, bits);
         });
         return;
     }
@@ -267,7 +284,7 @@ __global__ __launch_bounds__(256) void nms_stream_a(const float* __restrict__ R,
         const int ya = clampi(y - 1, H), yc = clampi(y + 1, H);
         const uint32_t bits = nms_bits_edges(row(ya), row(y), row(yc), px(ya, xl), px(ya, xr), px(y, xl), px(y, xr),
                                              px(yc, xl), px(yc, xr), tau);
-        *reinterpret_cast<uint32_t*>(out + (size_t)y * mp) = bits;
+        put(y, bits);
     }
 }
 
@@ -278,15 +295,23 @@ bool supports_stream_a(const NmsArgs& a) {
 
 template <int TH, bool SM>
 hipError_t launch_stream_a(const NmsArgs& a) {
-    const int nstrips = a.W / 256;
+    const int nstrips = (a.W + 255) / 256;
     const int rows = (a.H + TH - 1) / TH;
     const long long nwaves = (long long)nstrips * rows;
     if (nwaves > 0x7ffffff0LL) return hipErrorInvalidValue;
     const long long blocks = (nwaves + 3) / 4;
     hipLaunchKernelGGL((nms_stream_a<TH, SM>), dim3(SM ? grid_pad8(blocks) : (unsigned)blocks), dim3(256), 0, a.st,
                        a.R, a.rp, a.M, a.mp, a.W, a.H, a.tau, nstrips, (int)nwaves);
-    if (nstrips * 256 < a.W) return launch_row4_bands(a, 0, nstrips * 256);
     return hipGetLastError();
+}
+
+// The default: strips of 8 rows from 256 columns on, rows of any alignment (their vector accesses need none; the
+// strip entries of the table refuse rows off 16 bytes), row4 for narrower images, the plain kernel for wider windows.
+// 8192^2: 115 us in strips of 64 rows, 63 in strips of 8 (more waves, each row still read about once);
+// 1919 x 1081, rows off 16 bytes: row4 11 us, strips 5.
+hipError_t launch_any(const NmsArgs& a) {
+    if (a.r != 1) return launch_plain(a);
+    return a.W >= 256 ? launch_stream_a<8, false>(a) : launch_row4(a);
 }
 
 const Variant<NmsArgs> kNms[] = {
@@ -301,6 +326,7 @@ const Variant<NmsArgs> kNms[] = {
     {"stream_a_t4", supports_stream_a, launch_stream_a<4, false>},
     {"stream_a_t32_sm", supports_stream_a, launch_stream_a<32, true>},
     {"stream_a_t16_sm", supports_stream_a, launch_stream_a<16, true>},
+    {"strips_any_t8", supports_plain, launch_any},
 };
 
 }  // namespace
@@ -310,6 +336,6 @@ const Variant<NmsArgs>* nms_variants(int* count) {
     return kNms;
 }
 
-int nms_default(const NmsArgs& a) { return supports_stream(a) ? 2 : supports_row4(a) ? 1 : 0; }
+int nms_default(const NmsArgs& a) { return a.r == 1 ? 11 : 0; }   // strips_any_t8
 
 }  // namespace icl
