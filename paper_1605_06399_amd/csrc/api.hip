@@ -794,6 +794,7 @@ icl_status icl_selected_variant_problem(const icl_problem* q, int* index) {
             CornersArgs a{};
             a.rg = radius;
             a.nr = 1;
+            a.W = width; a.H = height;
             deflt = corners_default(a);
             break;
         }

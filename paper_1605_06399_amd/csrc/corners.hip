@@ -25,6 +25,7 @@
 #include "harris_strip.hpp"
 #include "icl_device.hpp"
 #include "icl_internal.hpp"
+#include "tile_stage.hpp"
 
 namespace icl {
 namespace {
@@ -33,8 +34,9 @@ constexpr int CS_COLS = 240;   // mask columns per strip (60 lanes x 4)
 
 // Interior (strip, row block) pairs: strips s_lo .. s_hi and row blocks b_lo .. b_hi read
 // nothing outside the image (columns xm-8 .. xm+247, rows y0-r-2 .. y0+TH+r+1); the rest
-// form the border set.  Each set runs as its own launch, so the interior kernel carries no
-// border code (and keeps four waves per SIMD at r = 2).
+// form the border set.  One launch holds both, border items first: as a second launch they ran
+// after the interior ones with too few waves to fill the chip, each waiting on one row at a time: 8192^2,
+// r = 2, 123 + 41 us as two launches, 137 as one.  Rows of any alignment take the vector accesses.
 struct Region {
     int nstrips, nblocks;
     int s_lo, s_hi, b_lo, b_hi;   // interior ranges; empty when s_lo > s_hi or b_lo > b_hi
@@ -64,21 +66,27 @@ struct Region {
     }
 };
 
-// PART 1: the interior set (no clamping anywhere); PART 2: the border set.
-template <int RG, int TH, int PART>
-__global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ src, size_t sp, uint8_t* __restrict__ M,
+// The register budget: four waves per SIMD up to a window radius of 2 and three at 3 for the tall strips of
+// images that fill the chip; two for strips of 8 and 4 rows, whose launches have fewer waves than that.
+constexpr int cs_waves(int rg, int th) { return th <= 8 ? 2 : rg <= 2 ? 4 : 3; }
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+template <int RG, int TH>
+__global__ __launch_bounds__(64, cs_waves(RG, TH)) void corners_stream(const float* __restrict__ src, size_t sp, uint8_t* __restrict__ M,
                                                      size_t mp, float* __restrict__ resp, size_t rp, int W, int H,
                                                      const float* __restrict__ g, float k, float tau, Region rg_,
-                                                     int vec_img, int vec_mask, int vec_resp) {
+                                                     int nborder) {
     constexpr int NW = 2 * RG + 1;   // window taps = ring of pending response rows
     constexpr int D = NW;
     constexpr int NR = TH + 2;       // response rows y0-1 .. y0+TH
     constexpr int K = NR + 2 * RG;   // window rows walked
     const int lane = threadIdx.x;
     int strip, rb;
-    if constexpr (PART == 1) {
-        strip = rg_.s_lo + (int)(blockIdx.x % (unsigned)rg_.ni());
-        rb = rg_.b_lo + (int)(blockIdx.x / (unsigned)rg_.ni());
+    const bool interior = (int)blockIdx.x >= nborder;
+    if (interior) {
+        const unsigned i = blockIdx.x - (unsigned)nborder;
+        strip = rg_.s_lo + (int)(i % (unsigned)rg_.ni());
+        rb = rg_.b_lo + (int)(i / (unsigned)rg_.ni());
     } else {
         rg_.border_item((int)blockIdx.x, strip, rb);
     }
@@ -93,8 +101,8 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
     auto store_outputs = [&](int y, uint32_t bits, v4f r, bool fast) {
         if (!mask_lane) return;
         uint8_t* mrow = M + (size_t)y * mp + c;
-        if (fast && vec_mask) {
-            *reinterpret_cast<uint32_t*>(mrow) = bits;
+        if (fast || c + 4 <= W) {
+            *reinterpret_cast<u32_any*>(mrow) = bits;
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -102,8 +110,8 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
         }
         if (resp) {
             float* rrow = reinterpret_cast<float*>(reinterpret_cast<char*>(resp) + (size_t)y * rp) + c;
-            if (fast && vec_resp) {
-                *reinterpret_cast<v4f*>(rrow) = r;
+            if (fast || c + 4 <= W) {
+                *reinterpret_cast<v4f_any*>(rrow) = r;
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
@@ -116,16 +124,13 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
                    harris_response(a[0].z, a[1].z, a[2].z, k), harris_response(a[0].w, a[1].w, a[2].w, k));
     };
 
-    const bool inside_x = vec_img && c - 4 * lane >= 0 && xm - 8 + 256 <= W;
-    const bool inside_y = y0 - RG - 2 >= 0 && y0 + TH + RG + 1 <= H - 1;
-    if constexpr (PART == 1) {
-        if (!(inside_x && inside_y)) return;   // never taken: the host's interior set is exact
+    constexpr int MI = D >= 5 ? D : (D == 3 ? 6 : 5);   // image-row ring
+    if (interior) {
         // interior: every read in bounds, nothing clamped.  Window row kk is gradient row
         // y0 - 1 - r + kk, whose Sobel reads image rows y0 - 2 - r + kk + {0, 1, 2}.  The walk
         // is unrolled completely: ring slots and row indices are constants, no branch.
-        constexpr int MI = D >= 5 ? D : (D == 3 ? 6 : 5);   // image-row ring
         const char* col = reinterpret_cast<const char*>(src) + (size_t)c * 4;
-        auto image_row = [&](int y) { return *reinterpret_cast<const v4f*>(col + (size_t)y * sp); };
+        auto image_row = [&](int y) { return *reinterpret_cast<const v4f_any*>(col + (size_t)y * sp); };
         const int ybase = y0 - RG - 2;
         v4f img[MI];
 #pragma unroll
@@ -144,9 +149,9 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
                 const int m = kk - j;
                 if (m < 0 || m >= NR) continue;
                 const int slot = m % D;
-                acc[slot][0] += gw[j] * qa;
-                acc[slot][1] += gw[j] * qb;
-                acc[slot][2] += gw[j] * qc;
+                acc[slot][0] = fma4(gw[j], qa, acc[slot][0]);
+                acc[slot][1] = fma4(gw[j], qb, acc[slot][1]);
+                acc[slot][2] = fma4(gw[j], qc, acc[slot][2]);
             }
             if constexpr (kk >= 2 * RG) {
                 constexpr int m = kk - 2 * RG;   // response row y0 - 1 + m is complete
@@ -160,8 +165,7 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
             }
         });
         return;
-    } else {
-    if (inside_x && inside_y) return;   // never taken: interior items belong to the other launch
+    }
 
     // border strips and row blocks: clamped loads; products and responses of columns outside
     // the image are replaced by those of the nearest column inside
@@ -186,14 +190,11 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
         }
         return p;
     };
+    // image row y, read clamped; its pixels are put in place where they are used, so that loads stay in flight
     auto image_row = [&](int y) {
-        const char* row = reinterpret_cast<const char*>(src) + (size_t)clampi(y, H) * sp;
-        if (inside_x) return *reinterpret_cast<const v4f*>(row + (size_t)c * 4);
-        v4f v;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const float*>(row + (size_t)clampi(c + q, W) * 4);
-        return v;
+        return load4_clamped<F32>(src, (size_t)clampi(y, H) * sp, W, c);
     };
+    auto px = [&](v4f v) { return fix4_clamped(v, W, c); };
     // window row kk is gradient row clamp(y0 - 1 - r + kk): a repeated gradient row reuses
     // the last products; the image rows around gradient row gr are clamp(gr - 1), gr, clamp(gr + 1)
     auto wrow = [&](int kk) { return clampi(y0 - 1 - RG + kk, H); };
@@ -204,33 +205,37 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
         qb = hwin<RG>(clamp_cols(pb), gw);
         qc = hwin<RG>(clamp_cols(pc), gw);
     };
+    // ring slot i % MI: image row y0 - 2 - r + i, which window row kk reads at i = kk, kk + 1, kk + 2 where its
+    // gradient row is its own (not a repeated one)
+    auto ring_row = [&](int i) { return image_row(y0 - 2 - RG + i); };
+    static_assert(MI % D == 0, "a step's ring slots are constants");
     const int g0 = wrow(0);
-    v4f ra = image_row(g0 - 1), rb = image_row(g0), rc = image_row(g0 + 1);
+    v4f img[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) img[i] = ring_row(i);
     v4f qa, qb, qc;
-    products(ra, rb, rc, qa, qb, qc);
+    if (y0 - 1 - RG >= 0 && g0 < H - 1) products(px(img[0]), px(img[1]), px(img[2 % MI]), qa, qb, qc);
+    else products(px(image_row(g0 - 1)), px(image_row(g0)), px(image_row(g0 + 1)), qa, qb, qc);
     v4f acc[D][3];
 #pragma unroll
     for (int u = 0; u < D; ++u) acc[u][0] = acc[u][1] = acc[u][2] = mk4(0.f, 0.f, 0.f, 0.f);
     v4f prev = mk4(0.f, 0.f, 0.f, 0.f), cur = prev;
-    for (int kb = 0; kb < K; kb += D) {
-        static_for<D>([&](auto u_c) {
+    for (int kb = 0; kb < K; kb += MI) {
+        static_for<MI>([&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;
             const int kk = kb + u;
             if (kk >= K) return;
-            if (kk > 0 && wrow(kk) != wrow(kk - 1)) {
-                ra = rb;
-                rb = rc;
-                rc = image_row(wrow(kk) + 1);
-                products(ra, rb, rc, qa, qb, qc);
-            }
+            if (kk > 0 && wrow(kk) != wrow(kk - 1))
+                products(px(img[u]), px(img[(u + 1) % MI]), px(img[(u + 2) % MI]), qa, qb, qc);
+            img[u] = ring_row(kk + MI);
 #pragma unroll
             for (int j = 0; j < NW; ++j) {
                 const int m = kk - j;
                 if (m < 0 || m >= NR) continue;
                 const int slot = ((u - j) % D + D) % D;
-                acc[slot][0] += gw[j] * qa;
-                acc[slot][1] += gw[j] * qb;
-                acc[slot][2] += gw[j] * qc;
+                acc[slot][0] = fma4(gw[j], qa, acc[slot][0]);
+                acc[slot][1] = fma4(gw[j], qb, acc[slot][1]);
+                acc[slot][2] = fma4(gw[j], qc, acc[slot][2]);
             }
             if (kk >= 2 * RG) {
                 constexpr int slot = ((u - 2 * RG) % D + D) % D;
@@ -251,7 +256,6 @@ __global__ __launch_bounds__(64) void corners_stream(const float* __restrict__ s
             }
         });
     }
-    }   // PART 2
 }
 
 bool supports_stream(const CornersArgs& a) {
@@ -260,26 +264,19 @@ bool supports_stream(const CornersArgs& a) {
 
 template <int RG, int TH>
 hipError_t launch_stream_R(const CornersArgs& a) {
-    const int vec_img = ((uintptr_t)a.src % 16 == 0) && (a.sp % 16 == 0);
-    const int vec_mask = ((uintptr_t)a.M % 4 == 0) && (a.mp % 4 == 0);
-    const int vec_resp = a.resp && ((uintptr_t)a.resp % 16 == 0) && (a.rp % 16 == 0);
     Region r{};
     r.nstrips = (a.W + CS_COLS - 1) / CS_COLS;
     r.nblocks = (a.H + TH - 1) / TH;
     if ((long long)r.nstrips * r.nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
     // interior strips s: s >= 1 and s * 240 + 248 <= W (columns xm-8 .. xm+247 inside)
     r.s_lo = 1;
-    r.s_hi = (vec_img && a.W >= 248) ? (a.W - 248) / CS_COLS : 0;
+    r.s_hi = a.W >= 248 ? (a.W - 248) / CS_COLS : 0;
     // interior row blocks b: b * TH >= r + 2 and b * TH + TH + r + 1 <= H - 1
     r.b_lo = (RG + 2 + TH - 1) / TH;
     const int top = a.H - 2 - RG - TH;
     r.b_hi = top >= 0 ? top / TH : -1;
-    if (r.interior() > 0)
-        hipLaunchKernelGGL((corners_stream<RG, TH, 1>), dim3((unsigned)r.interior()), dim3(64), 0, a.st, a.src, a.sp,
-                           a.M, a.mp, a.resp, a.rp, a.W, a.H, a.g, a.k, a.tau, r, vec_img, vec_mask, vec_resp);
-    if (r.border() > 0)
-        hipLaunchKernelGGL((corners_stream<RG, TH, 2>), dim3((unsigned)r.border()), dim3(64), 0, a.st, a.src, a.sp,
-                           a.M, a.mp, a.resp, a.rp, a.W, a.H, a.g, a.k, a.tau, r, vec_img, vec_mask, vec_resp);
+    hipLaunchKernelGGL((corners_stream<RG, TH>), dim3((unsigned)(r.nstrips * r.nblocks)), dim3(64), 0, a.st, a.src, a.sp,
+                       a.M, a.mp, a.resp, a.rp, a.W, a.H, a.g, a.k, a.tau, r, (int)r.border());
     return hipGetLastError();
 }
 
@@ -331,6 +328,8 @@ const Variant<CornersArgs> kCorners[] = {
     {"stream_t24", supports_stream, launch_stream<24>},
     {"stream_t32", supports_stream, launch_stream<32>},
     {"stream_t12", supports_stream, launch_stream<12>},
+    {"stream_t8", supports_stream, launch_stream<8>},
+    {"stream_t4", supports_stream, launch_stream<4>},
 };
 
 }  // namespace
@@ -348,6 +347,14 @@ const Variant<CornersArgs>* corners_variants(int* count) {
     return kCorners;
 }
 
-int corners_default(const CornersArgs& a) { return supports_stream(a) ? 1 : 0; }
+// Strips of 16 rows where they give six waves per SIMD, 8 or 4 rows on smaller images: a wave is one chain of
+// TH + 2 (r + 1) rows, and what recomputed rows cost matters only once the chip is full.  r = 2, strips of 16 / 8
+// / 4 rows, us: 8192^2 137 / 165 / 250, 4000 x 3000 47 / 41 / 53, 3000 x 2000 40 / 26 / 31, 1919 x 1081
+// 38 / 24 / 18.
+int corners_default(const CornersArgs& a) {
+    if (!supports_stream(a)) return 0;
+    const long long waves = (long long)((a.W + CS_COLS - 1) / CS_COLS) * ((a.H + 15) / 16);
+    return waves >= 6144 ? 1 : waves >= 1024 ? 5 : 6;
+}
 
 }  // namespace icl

@@ -8,8 +8,15 @@ namespace icl {
 
 // R = Sxx Syy - Sxy^2 - k (Sxx + Syy)^2 (Section 6, Harris corner detection)
 __device__ __forceinline__ float harris_response(float sxx, float syy, float sxy, float k) {
+    // the roundings written out: left to the compiler, a kernel's unrolling decided which product is fused, and
+    // strips of another height got other last bits
     const float tr = sxx + syy;
-    return sxx * syy - sxy * sxy - k * tr * tr;
+    return fmaf(-(k * tr), tr, fmaf(sxx, syy, -(sxy * sxy)));
+}
+
+// acc + w p with one rounding per element, written out for the same reason
+__device__ __forceinline__ v4f fma4(float w, v4f p, v4f acc) {
+    return mk4(fmaf(w, p.x, acc.x), fmaf(w, p.y, acc.y), fmaf(w, p.z, acc.z), fmaf(w, p.w, acc.w));
 }
 
 // Horizontal window of radius RG over a lane's four columns, neighbours by DPP.
