@@ -32,49 +32,20 @@ namespace {
 
 constexpr int CS_COLS = 240;   // mask columns per strip (60 lanes x 4)
 
-// Interior (strip, row block) pairs: strips s_lo .. s_hi and row blocks b_lo .. b_hi read
-// nothing outside the image (columns xm-8 .. xm+247, rows y0-r-2 .. y0+TH+r+1); the rest
-// form the border set.  One launch holds both, border items first: as a second launch they ran
+// Interior strips read nothing outside the image (columns xm-8 .. xm+247, rows y0-r-2 ..
+// y0+TH+r+1); the rest form the border set.  One launch holds both, border items first: as a second launch they ran
 // after the interior ones with too few waves to fill the chip, each waiting on one row at a time: 8192^2,
 // r = 2, 123 + 41 us as two launches, 137 as one.  Rows of any alignment take the vector accesses.
-struct Region {
-    int nstrips, nblocks;
-    int s_lo, s_hi, b_lo, b_hi;   // interior ranges; empty when s_lo > s_hi or b_lo > b_hi
-    __host__ __device__ int ni() const { return s_hi >= s_lo ? s_hi - s_lo + 1 : 0; }
-    __host__ __device__ int nj() const { return b_hi >= b_lo ? b_hi - b_lo + 1 : 0; }
-    __host__ __device__ long long interior() const { return (long long)ni() * nj(); }
-    __host__ __device__ long long border() const { return (long long)nstrips * nblocks - interior(); }
-    // border work item idx -> (strip, row block): first the row blocks outside b_lo..b_hi
-    // across all strips, then the strips outside s_lo..s_hi across the interior row blocks
-    __device__ void border_item(int idx, int& strip, int& rb) const {
-        if (interior() == 0) {
-            strip = idx % nstrips;
-            rb = idx / nstrips;
-            return;
-        }
-        const int top = (nblocks - nj()) * nstrips;
-        if (idx < top) {
-            const int r = idx / nstrips;
-            strip = idx % nstrips;
-            rb = r < b_lo ? r : r + nj();
-        } else {
-            const int i2 = idx - top, edge_strips = nstrips - ni();
-            const int q = i2 % edge_strips;
-            rb = b_lo + i2 / edge_strips;
-            strip = q < s_lo ? q : q + ni();
-        }
-    }
-};
-
-// The register budget: four waves per SIMD up to a window radius of 2 and three at 3 for the tall strips of
-// images that fill the chip; two for strips of 8 and 4 rows, whose launches have fewer waves than that.
-constexpr int cs_waves(int rg, int th) { return th <= 8 ? 2 : rg <= 2 ? 4 : 3; }
+// The register budget: two waves per SIMD for strips of 8 and 4 rows, whose launches have few waves, else three from a
+// window radius of 2 on (four spill: 5000 x 4000, r = 2, strips of 16 rows 69 us, three 51) and four below; the strips of
+// 32 rows, for images that fill the chip many times, are better off with four (8192^2, r = 2: 133 us, three 140).
+constexpr int cs_waves(int rg, int th) { return th <= 8 ? 2 : rg <= 1 || (rg == 2 && th == 32) ? 4 : 3; }
 typedef uint32_t u32_any __attribute__((aligned(1)));
 
 template <int RG, int TH>
 __global__ __launch_bounds__(64, cs_waves(RG, TH)) void corners_stream(const float* __restrict__ src, size_t sp, uint8_t* __restrict__ M,
                                                      size_t mp, float* __restrict__ resp, size_t rp, int W, int H,
-                                                     const float* __restrict__ g, float k, float tau, Region rg_,
+                                                     const float* __restrict__ g, float k, float tau, StripRegion rg_,
                                                      int nborder) {
     constexpr int NW = 2 * RG + 1;   // window taps = ring of pending response rows
     constexpr int D = NW;
@@ -176,14 +147,14 @@ __global__ __launch_bounds__(64, cs_waves(RG, TH)) void corners_stream(const flo
     const int e1 = (W - 1 - (xm - 8)) & 3;              // ... as element e1
     auto clamp_cols = [&](v4f p) -> v4f {
         if (left) {
-            const float v0 = __shfl(p.x, l0 < 0 ? 0 : (l0 > 63 ? 63 : l0));
+            const float v0 = lane_value(p.x, l0 < 0 ? 0 : (l0 > 63 ? 63 : l0));
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (c + q < 0) p[q] = v0;
         }
         if (right) {
             const float sel = e1 == 0 ? p.x : (e1 == 1 ? p.y : (e1 == 2 ? p.z : p.w));
-            const float v1 = __shfl(sel, l1 < 0 ? 0 : (l1 > 63 ? 63 : l1));
+            const float v1 = lane_value(sel, l1 < 0 ? 0 : (l1 > 63 ? 63 : l1));
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (c + q >= W) p[q] = v1;
@@ -264,7 +235,7 @@ bool supports_stream(const CornersArgs& a) {
 
 template <int RG, int TH>
 hipError_t launch_stream_R(const CornersArgs& a) {
-    Region r{};
+    StripRegion r{};
     r.nstrips = (a.W + CS_COLS - 1) / CS_COLS;
     r.nblocks = (a.H + TH - 1) / TH;
     if ((long long)r.nstrips * r.nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -347,14 +318,15 @@ const Variant<CornersArgs>* corners_variants(int* count) {
     return kCorners;
 }
 
-// Strips of 16 rows where they give six waves per SIMD, 8 or 4 rows on smaller images: a wave is one chain of
-// TH + 2 (r + 1) rows, and what recomputed rows cost matters only once the chip is full.  r = 2, strips of 16 / 8
-// / 4 rows, us: 8192^2 137 / 165 / 250, 4000 x 3000 47 / 41 / 53, 3000 x 2000 40 / 26 / 31, 1919 x 1081
-// 38 / 24 / 18.
+// The strips' height by the number of waves that strips of 16 rows would give: a wave is one chain of TH + 2 (r + 1)
+// rows, so that small images want short strips, and what the rows that two strips both walk cost matters only once the
+// chip is full.  r = 2, strips of 32 / 16 / 8 / 4 rows, us: 8192^2 (17920 waves) 133 / 143 / 163 / 210,
+// 8000 x 6000 (12750) 97 / 105 / 117 / -, 5000 x 4000 (5250) 73 / 51 / 56 / -, 4000 x 3000 (3196) 69 / 39 / 40 / 44
+// (r = 1 54 / 37 / 30 / 31, r = 3 71 / 57 / 54 / 60), 3000 x 2000 (1625) 62 / 31 / 24 / 27, 1919 x 1081 (544) 59 / 29 / 22 / 17.
 int corners_default(const CornersArgs& a) {
     if (!supports_stream(a)) return 0;
     const long long waves = (long long)((a.W + CS_COLS - 1) / CS_COLS) * ((a.H + 15) / 16);
-    return waves >= 6144 ? 1 : waves >= 1024 ? 5 : 6;
+    return waves >= 10000 ? 3 : waves >= 4096 ? 1 : waves >= 1024 ? 5 : 6;
 }
 
 }  // namespace icl

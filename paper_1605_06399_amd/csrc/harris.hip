@@ -20,11 +20,12 @@
 //   stream_t{TH}  : one wave per 248-column strip and TH rows, walking down the rows
 //                   with everything in registers (one float4 image load per lane and
 //                   row, neighbour columns by DPP lane shifts, rings of prefetched image
-//                   rows and of pending output rows); the 4-column left band and the
-//                   right remainder run through the tile kernel.  16-byte aligned rows.
+//                   rows and of pending output rows).  16-byte aligned rows, W >= 256.
+//   strips_t{TH}  : the same strips for rows of any alignment and any width.
 #include "harris_strip.hpp"
 #include "icl_device.hpp"
 #include "icl_internal.hpp"
+#include "tile_stage.hpp"
 
 namespace icl {
 namespace {
@@ -97,13 +98,10 @@ template <int RG, int TH> struct HTile {
     static constexpr int LDS_FLOATS = REGION1 + 3 * GH * GW;
 };
 
-// Tile columns come in two bands: the first n0 start at 0 (step TW) and write columns
-// below xl; the rest start at xr (step TW) and write columns below W.  The full image is
-// n0 = tiles_x, xl = W.
 template <int RG, int TH>
 __global__ __launch_bounds__(256) void harris_fused(const float* __restrict__ src, size_t sp, float* __restrict__ resp,
                                                     size_t rp, int W, int H, const float* __restrict__ g, float k,
-                                                    int tiles_x, int n0, int xl, int xr, int vec_ok) {
+                                                    int tiles_x, int vec_ok) {
     using G = HTile<RG, TH>;
     constexpr int TW = G::TW, HX = G::HX, HXA = G::HXA, IW = G::IW, IR = G::IR, GW = G::GW, GH = G::GH,
                   PY = G::PY;
@@ -114,8 +112,7 @@ __global__ __launch_bounds__(256) void harris_fused(const float* __restrict__ sr
     const int tid = threadIdx.x;
     const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
     const int tx = (int)(t % (unsigned)tiles_x);
-    const int x0 = tx < n0 ? tx * TW : xr + (tx - n0) * TW;
-    const int xe = tx < n0 ? xl : W;       // columns this tile may write
+    const int x0 = tx * TW;
     const int y0 = (int)(t / (unsigned)tiles_x) * TH;
 
     // 1. stage image rows y0-HX .. y0+TH+HX-1, columns x0-HXA .. x0+TW+HXA-1 (clamped)
@@ -216,133 +213,188 @@ __global__ __launch_bounds__(256) void harris_fused(const float* __restrict__ sr
             sc = fmaf(w, vc[py + j], sc);
         }
         const int y = y0 + ly * PY + py;
-        if (x < xe && y < H)
+        if (x < W && y < H)
             reinterpret_cast<float*>(reinterpret_cast<char*>(resp) + (size_t)y * rp)[x] = harris_response(sa, sb, sc, k);
     }
 }
 
-// Tile kernel over the bands [0, xl) and [xr, W) (xl = W: the whole image).
 template <int RG, int TH>
-hipError_t launch_fused_bands(const HarrisArgs& a, int xl, int xr) {
+hipError_t launch_fused_R(const HarrisArgs& a) {
     using G = HTile<RG, TH>;
-    const int n0 = (xl + G::TW - 1) / G::TW;
-    const int n1 = xl >= a.W ? 0 : (a.W - xr + G::TW - 1) / G::TW;
-    const int tiles_x = n0 + n1;
+    const int tiles_x = (a.W + G::TW - 1) / G::TW;
     const int tiles_y = (a.H + TH - 1) / TH;
     const int vec_ok = ((uintptr_t)a.src % 16 == 0) && (a.sp % 16 == 0);
     hipLaunchKernelGGL((harris_fused<RG, TH>), dim3(tiles_x * tiles_y), dim3(256), 0, a.st, a.src, a.sp, a.resp, a.rp,
-                       a.W, a.H, a.g, a.k, tiles_x, n0, xl, xr, vec_ok);
+                       a.W, a.H, a.g, a.k, tiles_x, vec_ok);
     return hipGetLastError();
 }
 
-template <int RG, int TH>
-hipError_t launch_fused_R(const HarrisArgs& a) {
-    return launch_fused_bands<RG, TH>(a, a.W, a.W);
-}
-
 // ------------------------------------------------------------------ streaming strips
-// One wave per strip of HS_COLS output columns and TH rows.  Lane l holds the four image
-// columns xs-4+4l .. xs-1+4l; lanes 1..62 own the strip's outputs, lanes 0 and 63 only
-// supply the left and right halo (3 columns suffice: Sobel 1 + window radius <= 3 = 4),
-// so every read of the strip is inside the image and nothing is clamped in x.  The wave
-// walks down the clamped window rows: per row it loads one float4 of the image per lane
-// (prefetched D rows ahead), forms the vertical Sobel parts from the last three image
-// rows, gets the neighbouring columns by DPP lane shifts, forms the three products and
-// their horizontal window sum, and adds that row into a ring of D = 2r+1 pending output
-// rows; the oldest completes and is written each step.  No LDS tile, no barrier.
+// One wave per strip of 248 output columns and TH rows.  Lane l holds the four image columns
+// xs-4+4l .. xs-1+4l; lanes 1..62 own the strip's outputs, lanes 0 and 63 only supply the left and right
+// halo (3 columns suffice: Sobel 1 + window radius <= 3 = 4).  The wave walks down the window rows: per
+// row it loads one float4 of the image per lane (a ring of rows in flight), gets the neighbouring columns
+// by DPP lane shifts, forms the three products and their horizontal window sum, and adds that row into a
+// ring of 2r+1 pending output rows; the oldest completes and is written each step.  No LDS tile, no
+// barrier; bound by HBM (8 B/px) on large images and by the length of a wave's chain of rows on small ones.
+//
+// Rows on 16 bytes of W >= 256: strip 0 is the left band of 4 columns, strips 1 .. n start at 4 + 248 (s - 1),
+// and those after them are the right remainder; the bands take the tile kernel's order of the Ix sum, so that
+// every column has the bits that it has always had.  Other images: strips at 248 s, all in the tile kernel's
+// order.  Strips and row blocks that reach past the image are the border set and come first in the launch.
+// As two launches (strips, then the bands through the tile kernel) the second had too few waves to
+// fill the chip.  r = 2, defaults before and now: 8192^2 154 -> 134 us, 3000 x 2000 37 -> 21, 1920 x 1080 32 -> 13,
+// 700 x 600 26 -> 11; 6001 x 5000 (rows off 16 bytes, tiles before) 118 -> 66.
 constexpr int HS_COLS = 248;   // output columns per strip (62 lanes x 4)
-constexpr int HS_XL = 4;       // left border band (the strips start here), done by the tile kernel
+constexpr int HS_XL = 4;       // the left band where the strips start on 16 bytes
 
-// One wave per work-group (the register allocation of a 64-lane launch bound keeps the
-// working set at four waves per SIMD without spills).
-template <int RG, int TH>
-__global__ __launch_bounds__(64) void harris_stream(const float* __restrict__ src, size_t sp, float* __restrict__ resp,
-                                                    size_t rp, int H, const float* __restrict__ g, float k,
-                                                    int nstrips) {
-    constexpr int NW = 2 * RG + 1;   // window taps = length of the ring of pending output rows
-    constexpr int K = TH + 2 * RG;   // window rows walked per strip
+// TILE: the interior strips take the tile kernel's order of the Ix sum (and strip 1 starts at 248)
+template <int RG, int TH, bool TILE>
+__global__ __launch_bounds__(64, TH <= 8 ? 2 : RG <= 1 ? 4 : 3) void harris_strips(
+    const float* __restrict__ src, size_t sp, float* __restrict__ resp, size_t rp, int W, int H,
+    const float* __restrict__ g, float k, StripRegion rg_, int nborder) {
+    constexpr int NW = 2 * RG + 1;   // window taps = ring of pending output rows
     constexpr int D = NW;
+    constexpr int K = TH + 2 * RG;   // window rows walked
+    constexpr int MI = D >= 5 ? D : (D == 3 ? 6 : 5);   // image-row ring
+    constexpr int X1 = TILE ? HS_COLS : HS_XL;          // where strip 1 starts
     const int lane = threadIdx.x;
-    const int strip = (int)(blockIdx.x % (unsigned)nstrips);
-    const int y0 = (int)(blockIdx.x / (unsigned)nstrips) * TH;
-    const int c = HS_XL + strip * HS_COLS - 4 + 4 * lane;
-    const char* col = reinterpret_cast<const char*>(src) + (size_t)c * 4;
-    auto image_row = [&](int y) { return *reinterpret_cast<const v4f*>(col + (size_t)y * sp); };
+    int strip, rb;
+    const bool interior = (int)blockIdx.x >= nborder;
+    if (interior) {
+        const unsigned i = blockIdx.x - (unsigned)nborder;
+        strip = rg_.s_lo + (int)(i % (unsigned)rg_.ni());
+        rb = rg_.b_lo + (int)(i / (unsigned)rg_.ni());
+    } else {
+        rg_.border_item((int)blockIdx.x, strip, rb);
+    }
+    const int y0 = rb * TH;
+    const int xs = strip > 0 ? X1 + (strip - 1) * HS_COLS : 0;
+    const int c = xs - 4 + 4 * lane;   // first image column of this lane
     float gw[NW];
 #pragma unroll
     for (int j = 0; j < NW; ++j) gw[j] = g[j];
     v4f acc[D][3];
 #pragma unroll
     for (int u = 0; u < D; ++u) acc[u][0] = acc[u][1] = acc[u][2] = mk4(0.f, 0.f, 0.f, 0.f);
-    const bool writer = lane >= 1 && lane <= 62;
-    char* out_col = reinterpret_cast<char*>(resp) + (size_t)c * 4;
-
-    // window row kk (phase u = kk mod D of the ring) feeds output rows kk - j; output row
-    // kk - 2r is then complete and is written
-    auto accumulate_emit = [&](int kk, auto u_c, v4f qa, v4f qb, v4f qc) {
-        constexpr int u = decltype(u_c)::value;
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const int m = kk - j;
-            if (m < 0 || m >= TH) continue;
-            const int slot = ((u - j) % D + D) % D;
-            acc[slot][0] += gw[j] * qa;
-            acc[slot][1] += gw[j] * qb;
-            acc[slot][2] += gw[j] * qc;
-        }
-        if (kk >= 2 * RG) {
-            constexpr int slot = ((u - 2 * RG) % D + D) % D;
-            const int y = y0 + kk - 2 * RG;
-            const v4f sa = acc[slot][0], sb = acc[slot][1], sc = acc[slot][2];
-            if (writer && y < H)
-                *reinterpret_cast<v4f*>(out_col + (size_t)y * rp) =
-                    mk4(harris_response(sa.x, sb.x, sc.x, k), harris_response(sa.y, sb.y, sc.y, k),
-                        harris_response(sa.z, sb.z, sc.z, k), harris_response(sa.w, sb.w, sc.w, k));
-            acc[slot][0] = acc[slot][1] = acc[slot][2] = mk4(0.f, 0.f, 0.f, 0.f);
-        }
+    auto add = [&](v4f (&a)[3], float w, v4f qa, v4f qb, v4f qc) {
+        a[0] = fma4(w, qa, a[0]);
+        a[1] = fma4(w, qb, a[1]);
+        a[2] = fma4(w, qc, a[2]);
     };
+    auto response = [&](v4f (&a)[3]) {   // and clears the sums
+        const v4f r = mk4(harris_response(a[0].x, a[1].x, a[2].x, k), harris_response(a[0].y, a[1].y, a[2].y, k),
+                          harris_response(a[0].z, a[1].z, a[2].z, k), harris_response(a[0].w, a[1].w, a[2].w, k));
+        a[0] = a[1] = a[2] = mk4(0.f, 0.f, 0.f, 0.f);
+        return r;
+    };
+    char* out_col = reinterpret_cast<char*>(resp) + (ptrdiff_t)c * 4;
 
-    if (y0 - RG - 1 >= 0 && y0 + TH + RG <= H - 1) {
-        // interior row block: window row kk is gradient row y0 - r + kk, whose Sobel reads
-        // image rows y0 - r - 1 + kk + {0, 1, 2}; those come from a ring of M image rows
-        // (image row i of the block in slot i mod M), each loaded M - 2 steps before use
-        // The walk is unrolled completely (TH is small), so every ring slot, row range and
-        // prefetch bound is a constant and the steady state has no branch.
-        constexpr int M = D >= 5 ? D : (D == 3 ? 6 : 5);
+    if (interior) {
+        // every read in bounds, nothing clamped.  Window row kk is gradient row y0 - r + kk, whose Sobel
+        // reads image rows y0 - r - 1 + kk + {0, 1, 2}.  The walk is unrolled completely: ring slots, row
+        // ranges and prefetch bounds are constants, no branch.
+        const char* col = reinterpret_cast<const char*>(src) + (size_t)c * 4;
+        auto image_row = [&](int y) { return *reinterpret_cast<const v4f_any*>(col + (size_t)y * sp); };
         const int ybase = y0 - RG - 1;
-        v4f img[M];
+        const bool writer = lane >= 1 && lane <= 62;
+        v4f img[MI];
 #pragma unroll
-        for (int i = 0; i < M; ++i) img[i] = image_row(ybase + i);
-        static_for<K>([&](auto k_c) {
+        for (int i = 0; i < MI; ++i) img[i] = image_row(ybase + i);
+        v4f hd[3];
+        if constexpr (TILE) {
+            hd[0] = row_difference(img[0]);
+            hd[1] = row_difference(img[1]);
+        }
+        static_for<K>([&](auto k_c) __attribute__((always_inline)) {
             constexpr int kk = decltype(k_c)::value;
-            v4f qa, qb, qc;
-            window_row<RG>(img[kk % M], img[(kk + 1) % M], img[(kk + 2) % M], gw, qa, qb, qc);
-            if constexpr (kk + M <= K + 1) img[kk % M] = image_row(ybase + kk + M);
-            accumulate_emit(kk, std::integral_constant<int, kk % D>{}, qa, qb, qc);
+            v4f pa, pb, pc;
+            if constexpr (TILE) {
+                hd[(kk + 2) % 3] = row_difference(img[(kk + 2) % MI]);
+                sobel_products_rows(hd[kk % 3], hd[(kk + 1) % 3], hd[(kk + 2) % 3], img[kk % MI], img[(kk + 2) % MI], pa,
+                                    pb, pc);
+            } else {
+                sobel_products(img[kk % MI], img[(kk + 1) % MI], img[(kk + 2) % MI], pa, pb, pc);
+            }
+            const v4f qa = hwin<RG>(pa, gw), qb = hwin<RG>(pb, gw), qc = hwin<RG>(pc, gw);
+            if constexpr (kk + MI <= K + 1) img[kk % MI] = image_row(ybase + kk + MI);
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                if (kk - j >= 0 && kk - j < TH) add(acc[(kk - j) % D], gw[j], qa, qb, qc);
+            if constexpr (kk >= 2 * RG) {
+                const v4f r = response(acc[(kk - 2 * RG) % D]);
+                if (writer) *reinterpret_cast<v4f_any*>(out_col + (size_t)(y0 + kk - 2 * RG) * rp) = r;
+            }
         });
         return;
     }
 
-    // row block at the top or bottom edge: window rows clamp to the gradient image, so a
-    // repeated gradient row reuses the last products and the image rows around gradient row
-    // g are clamp(g - 1), g, clamp(g + 1)
+    // border strips and row blocks: loads at clamped columns; the products of columns outside the image are
+    // replaced by those of the nearest column inside (window reads clamp on the gradient images)
+    const bool tile = TILE || strip < rg_.s_lo || strip > rg_.s_hi;   // the order of the Ix sum
+    const int xe = min(W, X1 + strip * HS_COLS);                      // columns up to the next strip's first
+    const bool left = xs < 4, right = xs + 252 > W;
+    const int l1 = (W - 1 - (xs - 4)) >> 2, e1 = (W - 1 - (xs - 4)) & 3;   // lane and element of column W - 1
+    auto clamp_cols = [&](v4f p) -> v4f {
+        if (left) {   // xs = 0: column 0 is lane 1's first
+            const float v0 = lane_value(p.x, 1);
+            if (lane == 0) p = mk4(v0, v0, v0, v0);
+        }
+        if (right) {
+            const float sel = e1 == 0 ? p.x : (e1 == 1 ? p.y : (e1 == 2 ? p.z : p.w));
+            const float v1 = lane_value(sel, l1 > 63 ? 63 : l1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (c + q >= W) p[q] = v1;
+        }
+        return p;
+    };
+    // image row y, read clamped; its pixels are put in place where they are used, so that loads stay in flight
+    auto image_row = [&](int y) { return load4_clamped<F32>(src, (size_t)clampi(y, H) * sp, W, c); };
+    auto px = [&](v4f v) { return fix4_clamped(v, W, c); };
     auto wrow = [&](int kk) { return clampi(y0 - RG + kk, H); };
-    const int g0 = wrow(0);
-    v4f ra = image_row(clampi(g0 - 1, H)), rb = image_row(g0), rc = image_row(clampi(g0 + 1, H));
     v4f qa, qb, qc;
-    window_row<RG>(ra, rb, rc, gw, qa, qb, qc);
-    for (int kb = 0; kb < K; kb += D) {
-        static_for<D>([&](auto u_c) {
+    auto products = [&](v4f ra, v4f rbw, v4f rc) {
+        v4f pa, pb, pc;
+        if (tile) sobel_products_rows(row_difference(ra), row_difference(rbw), row_difference(rc), ra, rc, pa, pb, pc);
+        else sobel_products(ra, rbw, rc, pa, pb, pc);
+        qa = hwin<RG>(clamp_cols(pa), gw);
+        qb = hwin<RG>(clamp_cols(pb), gw);
+        qc = hwin<RG>(clamp_cols(pc), gw);
+    };
+    // ring slot i % MI: image row y0 - 1 - r + i, which window row kk reads at i = kk, kk + 1, kk + 2 where its
+    // gradient row is its own (a repeated gradient row keeps the last products)
+    auto ring_row = [&](int i) { return image_row(y0 - 1 - RG + i); };
+    static_assert(MI % D == 0, "a step's ring slots are constants");
+    const int g0 = wrow(0);
+    v4f img[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) img[i] = ring_row(i);
+    if (y0 - RG >= 0 && y0 - RG <= H - 1) products(px(img[0]), px(img[1]), px(img[2 % MI]));
+    else products(px(image_row(g0 - 1)), px(image_row(g0)), px(image_row(g0 + 1)));
+    for (int kb = 0; kb < K; kb += MI) {
+        static_for<MI>([&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;
             const int kk = kb + u;
             if (kk >= K) return;
-            if (kk > 0 && wrow(kk) != wrow(kk - 1)) {
-                ra = rb;
-                rb = rc;
-                rc = image_row(clampi(wrow(kk) + 1, H));
-                window_row<RG>(ra, rb, rc, gw, qa, qb, qc);
+            if (kk > 0 && wrow(kk) != wrow(kk - 1)) products(px(img[u]), px(img[(u + 1) % MI]), px(img[(u + 2) % MI]));
+            img[u] = ring_row(kk + MI);
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                if (kk - j >= 0 && kk - j < TH) add(acc[((u - j) % D + D) % D], gw[j], qa, qb, qc);
+            if (kk >= 2 * RG) {
+                const v4f r = response(acc[((u - 2 * RG) % D + D) % D]);
+                const int y = y0 + kk - 2 * RG;
+                if (y >= H || lane < 1 || lane > 62) return;
+                float* o = reinterpret_cast<float*>(out_col + (size_t)y * rp);
+                if (c + 4 <= xe) {
+                    *reinterpret_cast<v4f_any*>(o) = r;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (c + q < xe) o[q] = r[q];
+                }
             }
-            accumulate_emit(kk, u_c, qa, qb, qc);
         });
     }
 }
@@ -352,26 +404,43 @@ bool supports_stream(const HarrisArgs& a) {
            (uintptr_t)a.resp % 16 == 0 && a.rp % 16 == 0;
 }
 
-template <int RG, int TH>
-hipError_t launch_stream_R(const HarrisArgs& a) {
-    const int nstrips = (a.W - HS_XL - 4) / HS_COLS;
-    const int xr = HS_XL + nstrips * HS_COLS;
-    const int rows = (a.H + TH - 1) / TH;
-    hipLaunchKernelGGL((harris_stream<RG, TH>), dim3((unsigned)(nstrips * rows)), dim3(64), 0, a.st, a.src, a.sp,
-                       a.resp, a.rp, a.H, a.g, a.k, nstrips);
-    // the two border bands with the tile kernel
-    return launch_fused_bands<RG, 16>(a, HS_XL, xr);
+template <int RG, int TH, bool TILE>
+hipError_t launch_strips_R(const HarrisArgs& a) {
+    constexpr int X1 = TILE ? HS_COLS : HS_XL;
+    StripRegion r{};
+    r.nstrips = a.W <= X1 ? 1 : 1 + (a.W - X1 + HS_COLS - 1) / HS_COLS;
+    r.nblocks = (a.H + TH - 1) / TH;
+    if ((long long)r.nstrips * r.nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    // interior strips s >= 1: X1 + (s - 1) * 248 + 252 <= W (columns xs-4 .. xs+251 inside)
+    r.s_lo = 1;
+    r.s_hi = a.W >= X1 + 252 ? 1 + (a.W - X1 - 252) / HS_COLS : 0;
+    // interior row blocks b: b TH >= r + 1 and b TH + TH + r <= H - 1
+    r.b_lo = (RG + 1 + TH - 1) / TH;
+    const int top = a.H - 1 - RG - TH;
+    r.b_hi = top >= 0 ? top / TH : -1;
+    hipLaunchKernelGGL((harris_strips<RG, TH, TILE>), dim3((unsigned)(r.nstrips * r.nblocks)), dim3(64), 0, a.st, a.src,
+                       a.sp, a.resp, a.rp, a.W, a.H, a.g, a.k, r, (int)r.border());
+    return hipGetLastError();
+}
+
+template <int TH, bool TILE>
+hipError_t launch_strips(const HarrisArgs& a) {
+    switch (a.rg) {
+        case 0: return launch_strips_R<0, TH, TILE>(a);
+        case 1: return launch_strips_R<1, TH, TILE>(a);
+        case 2: return launch_strips_R<2, TH, TILE>(a);
+        case 3: return launch_strips_R<3, TH, TILE>(a);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int TH>
-hipError_t launch_stream(const HarrisArgs& a) {
-    switch (a.rg) {
-        case 0: return launch_stream_R<0, TH>(a);
-        case 1: return launch_stream_R<1, TH>(a);
-        case 2: return launch_stream_R<2, TH>(a);
-        case 3: return launch_stream_R<3, TH>(a);
-        default: return hipErrorInvalidValue;
-    }
+hipError_t launch_stream(const HarrisArgs& a) { return launch_strips<TH, false>(a); }
+
+// rows of any alignment and images of any width
+template <int TH>
+hipError_t launch_any(const HarrisArgs& a) {
+    return supports_stream(a) ? launch_strips<TH, false>(a) : launch_strips<TH, true>(a);
 }
 
 template <int TH>
@@ -396,6 +465,10 @@ const Variant<HarrisArgs> kHarris[] = {
     {"stream_t32", supports_stream, launch_stream<32>},
     {"stream_t16", supports_stream, launch_stream<16>},
     {"stream_t12", supports_stream, launch_stream<12>},
+    {"strips_t16", supports_fused, launch_any<16>},
+    {"strips_t12", supports_fused, launch_any<12>},
+    {"strips_t8", supports_fused, launch_any<8>},
+    {"strips_t4", supports_fused, launch_any<4>},
 };
 
 }  // namespace
@@ -407,7 +480,18 @@ const Variant<HarrisArgs>* harris_variants(int* count) {
     return kHarris;
 }
 
-// strip variant with 32-row blocks where the rows allow it, else the 64 x 16 tile kernel
-int harris_default(const HarrisArgs& a) { return supports_stream(a) ? 5 : supports_fused(a) ? 1 : 0; }
+// The tile kernel below 256 columns and, for rows off 16 bytes, below 1024 waves of 16-row strips (its 4 waves
+// share a tile, so a small image is done sooner: 1919 x 1081, r = 2, 12.1 us against 12.7 in strips of 4 rows; 3001 x
+// 2001 27 against 21 in strips of 8; 6001 x 5000 115 against 66).  Aligned rows keep to strips at every size, as
+// the two kernels round differently.  Strips of 12 or 16 rows where they give four waves per SIMD, 8 or 4 rows on smaller
+// images: a wave is one chain of TH + 2 r rows.  r = 2, strips of 32 / 16 / 8 / 4 rows, us: 8192^2 132 / 134 / 148 / 182,
+// 5000 x 4000 63 / 47 / 50 / -, 4000 x 3000 50 / 37 / 35 / 36, 3000 x 2000 43 / 28 / 21 / 23, 1920 x 1080 39 / 24 / 16 / 13;
+// 16 / 12 rows at 8192^2: r = 3 156 / 165, r = 1 128 / 123.
+int harris_default(const HarrisArgs& a) {
+    if (!supports_fused(a)) return 0;
+    const long long waves = (long long)(1 + a.W / HS_COLS) * ((a.H + 15) / 16);
+    if (!supports_stream(a) && (a.W < 256 || waves < 1024)) return 1;
+    return waves >= 4096 ? (a.rg >= 2 ? 8 : 9) : waves >= 1024 ? 10 : 11;
+}
 
 }  // namespace icl

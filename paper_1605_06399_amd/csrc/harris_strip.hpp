@@ -6,6 +6,42 @@
 
 namespace icl {
 
+// The (strip, row block) pairs of a launch: strips s_lo .. s_hi and row blocks b_lo .. b_hi form
+// the interior set, whose reads need no clamp; the rest are the border set.
+struct StripRegion {
+    int nstrips, nblocks;
+    int s_lo, s_hi, b_lo, b_hi;   // interior ranges; empty when s_lo > s_hi or b_lo > b_hi
+    __host__ __device__ int ni() const { return s_hi >= s_lo ? s_hi - s_lo + 1 : 0; }
+    __host__ __device__ int nj() const { return b_hi >= b_lo ? b_hi - b_lo + 1 : 0; }
+    __host__ __device__ long long interior() const { return (long long)ni() * nj(); }
+    __host__ __device__ long long border() const { return (long long)nstrips * nblocks - interior(); }
+    // border work item idx -> (strip, row block): first the row blocks outside b_lo..b_hi
+    // across all strips, then the strips outside s_lo..s_hi across the interior row blocks
+    __device__ void border_item(int idx, int& strip, int& rb) const {
+        if (interior() == 0) {
+            strip = idx % nstrips;
+            rb = idx / nstrips;
+            return;
+        }
+        const int top = (nblocks - nj()) * nstrips;
+        if (idx < top) {
+            const int r = idx / nstrips;
+            strip = idx % nstrips;
+            rb = r < b_lo ? r : r + nj();
+        } else {
+            const int i2 = idx - top, edge_strips = nstrips - ni();
+            const int q = i2 % edge_strips;
+            rb = b_lo + i2 / edge_strips;
+            strip = q < s_lo ? q : q + ni();
+        }
+    }
+};
+
+// the value of a wave-uniform lane, without a trip through LDS
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), __builtin_amdgcn_readfirstlane(lane)));
+}
+
 // R = Sxx Syy - Sxy^2 - k (Sxx + Syy)^2 (Section 6, Harris corner detection)
 __device__ __forceinline__ float harris_response(float sxx, float syy, float sxy, float k) {
     // the roundings written out: left to the compiler, a kernel's unrolling decided which product is fused, and
@@ -47,6 +83,23 @@ __device__ __forceinline__ void sobel_products(const v4f ra, const v4f rb, const
     const float vsl = lane_from_left(vs.w), vsr = lane_from_right(vs.x);
     const float vdl = lane_from_left(vd.w), vdr = lane_from_right(vd.x);
     const v4f ix = mk4(vs.y - vsl, vs.z - vs.x, vs.w - vs.y, vsr - vs.z);
+    const v4f iy = mk4(vdl + 2.f * vd.x + vd.y, vd.x + 2.f * vd.y + vd.z, vd.y + 2.f * vd.z + vd.w,
+                       vd.z + 2.f * vd.w + vdr);
+    pa = ix * ix;
+    pb = iy * iy;
+    pc = ix * iy;
+}
+
+// The same from the tile kernel's order of the Ix sum, (right - left) per row first; hda, hdb, hdc are
+// those differences of the three rows.  The two orders differ in the last bits.
+__device__ __forceinline__ v4f row_difference(v4f p) {
+    return mk4(p.y - lane_from_left(p.w), p.z - p.x, p.w - p.y, lane_from_right(p.x) - p.z);
+}
+__device__ __forceinline__ void sobel_products_rows(const v4f hda, const v4f hdb, const v4f hdc, const v4f ra,
+                                                    const v4f rc, v4f& pa, v4f& pb, v4f& pc) {
+    const v4f vd = rc - ra;
+    const float vdl = lane_from_left(vd.w), vdr = lane_from_right(vd.x);
+    const v4f ix = hda + 2.f * hdb + hdc;
     const v4f iy = mk4(vdl + 2.f * vd.x + vd.y, vd.x + 2.f * vd.y + vd.z, vd.y + 2.f * vd.z + vd.w,
                        vd.z + 2.f * vd.w + vdr);
     pa = ix * ix;

@@ -70,3 +70,40 @@ def test_corner_strip_heights_agree(rg, W, pad, off):
             if ref is None:
                 ref = R
             assert torch.equal(R.view(torch.int32), ref.view(torch.int32)), f"{name} {H}x{W}: response bits"
+
+
+@pytest.mark.parametrize("rg", [0, 1, 2, 3])
+@pytest.mark.parametrize("W,pad,off", [(3, 0, 0), (251, 1, 1), (256, 0, 0), (260, 4, 0), (499, 0, 3), (503, 1, 0), (752, 0, 0)])
+def test_harris_strip_heights_agree(rg, W, pad, off):
+    """Every column has one rounding whatever the strip's height: the tile kernel's for rows off 16 bytes and, of
+    aligned rows, for the left 4 columns and those right of the last whole strip."""
+    g = synth.gaussian_taps(rg, 1.0)
+    taps = torch.from_numpy(g).cuda()
+    names = [B.icl_variant_name(B.ICL_OP_HARRIS, v) for v in range(B.icl_variant_count(B.ICL_OP_HARRIS))]
+    aligned = W >= 256 and (W + pad) % 4 == 0 and off % 4 == 0 and W % 4 == 0
+    xr = 4 + (W - 8) // 248 * 248
+    for H in (1, 3, 4, 5, 11, 22, 37):
+        xd, x64 = storage(synth.image_uniform(66 + rg, H, W), "f32")
+        x = padded_view(xd, pad, off)
+        out = {}
+        for v, name in enumerate(names):
+            if not (name == "fused_t16" or name.startswith("strips") or (aligned and name.startswith("stream"))):
+                continue
+            R = torch.empty((H, W), dtype=torch.float32, device="cuda")
+            B.check(B.icl_force_variant(B.ICL_OP_HARRIS, v))
+            try:
+                T.harris(x, taps, out=R)
+            finally:
+                B.icl_force_variant(B.ICL_OP_HARRIS, -1)
+            out[name] = R.view(torch.int32)
+        bound = oracle.harris_f32_bound(x64, g, 0.04)
+        err = np.abs(out["strips_t8"].view(torch.float32).cpu().numpy() - oracle.harris(x64, g, 0.04))
+        assert (err <= bound).all(), f"{H}x{W}"
+        for name, R in out.items():
+            if name != "fused_t16":
+                assert torch.equal(R, out["strips_t8"]), f"{name} {H}x{W}"
+        tile = out["fused_t16"]
+        if aligned:
+            assert torch.equal(out["strips_t8"][:, :4], tile[:, :4]) and torch.equal(out["strips_t8"][:, xr:], tile[:, xr:])
+        else:
+            assert torch.equal(out["strips_t8"], tile), f"{H}x{W}"
