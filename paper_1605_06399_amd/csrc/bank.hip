@@ -247,11 +247,11 @@ __global__ __launch_bounds__(256) void bank_bwd_edge_k(const float* __restrict__
                                                        float* __restrict__ gx, int F, int H, int W, int top,
                                                        int bottom, int left, int per_img,
                                                        const float* __restrict__ scale) {
-    constexpr int N = 2 * R + 1, L = EDGE_SEG + 2 * R;
-    __shared__ float wl[64 * N * N];
-    __shared__ float strip[L * (R + 1)];
-    __shared__ float tab[(R + 1) * N];   // this side's one-axis box sums of the current filter
-    __shared__ float ctab[2][(R + 1) * (R + 1)];   // 2-D box sums of the left / right corner
+    constexpr int N = 2 * R + 1, L = EDGE_SEG + 2 * R, FMAX = 64;
+    __shared__ float wl[FMAX * N * N];
+    __shared__ float strips[2][L * (R + 1) + 1];           // [depth][along], of this filter and of the next
+    __shared__ float tab[FMAX * (R + 1) * N];              // this side's one-axis box sums
+    __shared__ float ctab[FMAX * 2 * (R + 1) * (R + 1)];   // 2-D box sums of the left / right corner
     for (int i = threadIdx.x; i < F * N * N; i += 256) wl[i] = w[i];
     const int n = blockIdx.x / per_img;
     int s = blockIdx.x - n * per_img, side, a0;
@@ -293,62 +293,87 @@ __global__ __launch_bounds__(256) void bank_bwd_edge_k(const float* __restrict__
     const int t = (int)threadIdx.x;
     const size_t hw = (size_t)H * W;
     // The strip of filter f+1 is loaded into registers while filter f is computed (thread
-    // t holds strip entries t, t + 256, ...), so the global loads of the whole walk overlap.
+    // t holds strip entries t, t + 256, ...), so the global loads of the whole walk overlap (four filters ahead
+    // measures the same).
+    // Entries run along the rows of the image: depth by depth for the top and bottom, across the depth first
+    // for the left and right.
     constexpr int NPRE = (L * (R + 1) + 255) / 256;
     float pre[NPRE];
-    auto fetch = [&](int f) {
-        const float* g = gy + ((size_t)n * F + f) * hw;
+    const float* from[NPRE];   // in the plane of the filter fetched next
+    int to[NPRE];              // in the strip; entries outside the image go past its end and stay zero in it
+    for (int i = t; i < 2 * (L * (R + 1) + 1); i += 256) (&strips[0][0])[i] = 0.f;
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u) {
+        const int idx = t + 256 * u;
+        const int ai = side < 2 ? idx % L : idx / (R + 1), d = side < 2 ? idx / L : idx % (R + 1);
+        const int aa = a0 - R + ai;
+        const bool in = idx < L * (R + 1) && d < D && aa >= 0 && aa < along;
+        int x, y;
+        pixel(in ? aa : 0, in ? d : 0, x, y);
+        from[u] = gy + (size_t)n * F * hw + (size_t)y * W + x;
+        to[u] = in ? d * L + ai : L * (R + 1);
+    }
+    auto fetch = [&]() {
 #pragma unroll
         for (int u = 0; u < NPRE; ++u) {
-            const int idx = t + 256 * u;
-            const int ai = idx / D, d = idx - ai * D, aa = a0 - R + ai;
-            float v = 0.f;
-            if (idx < L * D && aa >= 0 && aa < along) {
-                int x, y;
-                pixel(aa, d, x, y);
-                v = g[(size_t)y * W + x];
-            }
-            pre[u] = v;
+            pre[u] = *from[u];
+            from[u] += hw;
         }
     };
-    fetch(0);
+    fetch();
+    __syncthreads();   // the taps and the zeros
+    // top: sum over rows ky = -r .. -d; bottom: ky = d .. r; left / right: the same over columns.  Each box is
+    // summed directly, in ascending tap order.  All filters' boxes at once: as one filter's between two barriers they
+    // were a chain of LDS reads that every filter waited for (32 x 16 x 1024^2, r = 4: 82 us, now 52).
+    for (int i = t; i < F * (R + 1) * N; i += 256) {
+        const int f = i / ((R + 1) * N), e = i - f * ((R + 1) * N), d = e / N, k = e - d * N;
+        const int lo = side == 0 || side == 2 ? 0 : R + d, hi = side == 0 || side == 2 ? R - d : 2 * R;
+        const float* wf = wl + f * N * N + (side < 2 ? k : k * N);
+        const int step = side < 2 ? N : 1;
+        float b = 0.f;
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const float next = b + wf[m * step];
+            b = m >= lo && m <= hi ? next : b;
+        }
+        tab[i] = b;
+    }
+    // corner boxes: rows -r .. -dy (top) or dy .. r (bottom), columns -r .. -dx (left corner) or dx .. r (right corner)
+    if (has_left || has_right)
+        for (int i = t; i < F * 2 * (R + 1) * (R + 1); i += 256) {
+            const int f = i / (2 * (R + 1) * (R + 1)), u = i - f * (2 * (R + 1) * (R + 1));
+            const int c = u / ((R + 1) * (R + 1)), e = u - c * (R + 1) * (R + 1);
+            const int dy = e / (R + 1), dx = e - dy * (R + 1);
+            const int rlo = side == 0 ? 0 : R + dy, rhi = side == 0 ? R - dy : 2 * R;
+            const int clo = c == 0 ? 0 : R + dx, chi = c == 0 ? R - dx : 2 * R;
+            const float* wf = wl + f * N * N;
+            float b = 0.f;
+#pragma unroll
+            for (int m = 0; m < N; ++m)
+#pragma unroll
+                for (int l = 0; l < N; ++l) {
+                    const float next = b + wf[m * N + l];
+                    b = m >= rlo && m <= rhi && l >= clo && l <= chi ? next : b;
+                }
+            ctab[i] = b;
+        }
     float acc = 0.f;
     for (int f = 0; f < F; ++f) {
-        __syncthreads();   // taps staged; previous strip and table consumed
+        float* strip = strips[f & 1];   // its readers of two filters ago are behind the last barrier
 #pragma unroll
-        for (int u = 0; u < NPRE; ++u)
-            if (t + 256 * u < L * D) strip[t + 256 * u] = pre[u];
-        if (f + 1 < F) fetch(f + 1);
+        for (int u = 0; u < NPRE; ++u) strip[to[u]] = pre[u];
+        if (f + 1 < F) fetch();
         const float* wf = wl + f * N * N;
-        if (t < (R + 1) * N) {
-            // top: sum over rows ky = -r .. -d; bottom: ky = d .. r; left / right: the same
-            // over columns.  Each box is summed directly, in ascending tap order.
-            const int d = t / N, k = t - d * N;
-            const int lo = side == 0 || side == 2 ? 0 : R + d, hi = side == 0 || side == 2 ? R - d : 2 * R;
-            float b = 0.f;
-            for (int m = lo; m <= hi; ++m) b += side < 2 ? wf[m * N + k] : wf[k * N + m];
-            tab[t] = b;
-        }
-        {
-            // corner boxes: rows -r .. -dy (top) or dy .. r (bottom), columns -r .. -dx
-            // (left corner) or dx .. r (right corner), summed directly
-            const int u = t - 64, c = u / ((R + 1) * (R + 1)), e = u - c * (R + 1) * (R + 1);
-            if (u >= 0 && c < 2 && (c == 0 ? has_left : has_right)) {
-                const int dy = e / (R + 1), dx = e - dy * (R + 1);
-                const int rlo = side == 0 ? 0 : R + dy, rhi = side == 0 ? R - dy : 2 * R;
-                const int clo = c == 0 ? 0 : R + dx, chi = c == 0 ? R - dx : 2 * R;
-                float b = 0.f;
-                for (int m = rlo; m <= rhi; ++m)
-                    for (int l = clo; l <= chi; ++l) b += wf[m * N + l];
-                ctab[c][e] = b;
-            }
-        }
+        const float* tf = tab + f * (R + 1) * N;
+        const float* cf = ctab + f * 2 * (R + 1) * (R + 1);
         __syncthreads();
         if (!active) continue;
         if (fast) {
-            for (int d = 0; d < D; ++d) {
 #pragma unroll
-                for (int e = -R; e <= R; ++e) acc = fmaf(strip[(t + e + R) * D + d], tab[d * N + R - e], acc);
+            for (int d = 0; d <= R; ++d) {
+                if (d >= D) break;
+#pragma unroll
+                for (int e = -R; e <= R; ++e) acc = fmaf(strip[d * L + t + e + R], tf[d * N + R - e], acc);
             }
             continue;
         }
@@ -357,7 +382,7 @@ __global__ __launch_bounds__(256) void bank_bwd_edge_k(const float* __restrict__
             for (int dy = 0; dy < D; ++dy)
                 for (int dx = 0; dx < Dx; ++dx) {
                     const int px = c == 0 ? dx : W - 1 - dx;
-                    acc = fmaf(strip[(px - a0 + R) * D + dy], ctab[c][dy * (R + 1) + dx], acc);
+                    acc = fmaf(strip[dy * L + px - a0 + R], cf[(c * (R + 1) + dy) * (R + 1) + dx], acc);
                 }
             continue;
         }
@@ -375,7 +400,7 @@ __global__ __launch_bounds__(256) void bank_bwd_edge_k(const float* __restrict__
                     case 2: ai = py - a0 + R; d = px; break;
                     default: ai = py - a0 + R; d = W - 1 - px; break;
                 }
-                acc = fmaf(strip[ai * D + d], b, acc);
+                acc = fmaf(strip[d * L + ai], b, acc);
             }
         }
     }
