@@ -222,7 +222,7 @@ WORKLOAD_KERNELS = [
     ("bank", r"bank_fwd_(mfma_k<4, true, \d+, (?:true|false)>|pers_k<4, true>|sse_tpre_k<4>)", "fwd_sse:{0}",
      ["bank.hip"],
      4 * (_BANK[0] * _BANK[2] + 2 * _BANK[0] * _BANK[1] * _BANK[2])),
-    ("bank", r"bank_bwd_in_(pers_k|k)<4>", "bwd_input:{0}", ["bank.hip"],
+    ("bank", r"bank_bwd_in_(mfma_k|pers_k|k)<4>", "bwd_input:{0}", ["bank.hip"],
      4 * (_BANK[0] * _BANK[1] * _BANK[2] + _BANK[0] * _BANK[2])),
     ("bank", r"bank_bwd_(wm_k<4, \d, (?:true|false)(?:, (?:true|false))?>|w4_k<4, \d, 16>)", "bwd_filter:{0}",
      ["bank.hip"],

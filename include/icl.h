@@ -435,6 +435,8 @@ icl_math icl_get_math(void);
 /* Arithmetic a variant computes in (static string, NULL if out of range):
  *   "fp32_valu"   float32 vector FMA          "fp32_mfma"  float32 matrix instructions
  *   "fp16x3_mfma" float16 hi/lo split on the matrix cores (see ICL_MATH_F16_SPLIT)
+ *   "bf16x3_mfma" float32 operands in three exact bfloat16 parts on the matrix cores, float32 accumulation; the
+ *                 error is that of float32 sums or less (icl_bank_bwd_input)
  *   "int32_valu"  exact integer arithmetic (icl_conv2d_u8): 32-bit, or bytes on the matrix cores with
  *                 32-bit accumulation ("mfma_i8") */
 const char* icl_variant_arith(icl_op op, int index);

@@ -67,6 +67,7 @@ static const char* arith_of(icl_op op, const char* name) {
     if (!name) return nullptr;
     if (op == ICL_OP_CONV2D_U8) return "int32_valu";
     if (std::strncmp(name, "mfma_f16", 8) == 0) return "fp16x3_mfma";
+    if (std::strncmp(name, "mfma_bf16x3", 11) == 0) return "bf16x3_mfma";   // float32 operands in three exact parts
     if (std::strstr(name, "mfma")) return "fp32_mfma";
     return "fp32_valu";
 }
@@ -768,6 +769,7 @@ icl_status icl_selected_variant_problem(const icl_problem* q, int* index) {
         case ICL_OP_HARRIS: {
             HarrisArgs a{};
             a.rg = radius;
+            a.W = width; a.H = height;
             deflt = harris_default(a);
             break;
         }

@@ -16,6 +16,8 @@
 //   bank_bwd_in    : same tiling; for each filter the gy tile (zero outside the image)
 //                    is staged and correlated with the flipped filter; the F sums
 //                    accumulate in registers and are stored once.
+//   bank_bwd_in_mfma (its own file): the same sums on the matrix cores, rows of gy split in three
+//                    exact bfloat16 parts.
 //   bank_bwd_edge  : recomputes the border pixels, where the clamp folds padded positions
 //                    onto q, as a correlation of gy with box sums of the taps; one
 //                    work-group per 256-pixel border segment, gy strip staged in LDS.
@@ -1316,9 +1318,19 @@ bool supports_bwd_w(const BankArgs& a) {
 bool supports_bwd_wm(const BankArgs& a) { return supports_bwd_w(a) && a.f <= 16; }
 
 
+// on the matrix cores for radius 3 and 4 and up to 16 filters, else the FMA tiles
+template <int R> hipError_t edge_R(const BankArgs& a) { return launch_edge<R>(a); }
+hipError_t launch_edges(const BankArgs& a) { ICL_BANK_SWITCH(edge_R) }
+hipError_t launch_bwd_in_mfma(const BankArgs& a) {
+    if (!supports_bank_bwd_in_mfma(a)) return supports_pers(a) ? launch_bwd_in_pers(a) : launch_bwd_in(a);
+    const hipError_t e = launch_bank_bwd_in_mfma(a);
+    return e == hipSuccess ? launch_edges(a) : e;
+}
+
 const Variant<BankArgs> kBwdIn[] = {{"plain", supports_bank, launch_bwd_in_plain},
                                     {"tile64_p4x4_fold", supports_bank, launch_bwd_in},
-                                    {"pers_p4x4_fold", supports_pers, launch_bwd_in_pers}};
+                                    {"pers_p4x4_fold", supports_pers, launch_bwd_in_pers},
+                                    {"mfma_bf16x3_fold", supports_bank, launch_bwd_in_mfma}};
 const Variant<BankArgs> kBwdW[] = {{"wave_t32x64", supports_bwd_w, launch_bwd_w},
                                    {"block4_t64", supports_bwd_w, launch_bwd_w4},
                                    {"block4_t64x256", supports_bwd_w, launch_bwd_w4x4},
@@ -1748,7 +1760,19 @@ const Variant<BankArgs>* bank_bwd_filter_variants(int* count) {
 }
 
 int bank_fwd_default(const BankArgs& a) { return supports_mfma16(a) ? 4 : supports_pers(a) ? 2 : 1; }   // mfma_px_t64
-int bank_bwd_input_default(const BankArgs& a) { return supports_pers(a) ? 2 : 1; }
+// The matrix cores where they win: the FMA tiles' time grows with F (2r+1)^2, theirs is that of 16 filters whatever F is,
+// and a wave's row of products is long, so that the rows need to be many.  pers / mfma, us: 32 x F x 1024^2, r = 4,
+// F = 16 1269 / 909, F = 12 924 / 862, F = 9 710 / 796; 16 x 16 x 512^2 199 / 184; 8 x 16 x 512^2 125 / 127;
+// 2 x 16 x 1000^2 124 / 133; r = 3, 32 x 16 x 1024^2 874 / 753, 8 x 16 x 1024^2 234 / 220, 16 x 16 x 512^2 129 / 135.
+// A last strip that is mostly padding takes it back (20 x 12 x 871 x 158, r = 4: 164 / 169).
+int bank_bwd_input_default(const BankArgs& a) {
+    if (!supports_pers(a)) return 1;
+    const long long px = (long long)a.n * a.h * a.w, mpx = 1LL << 20;
+    const bool wide = (long long)((a.w + 127) / 128) * 128 * 5 <= 6LL * a.w;
+    const bool many = a.r == 4 ? (px >= 4 * mpx && a.f >= 14) || (px >= 16 * mpx && a.f >= 12)
+                               : a.r == 3 && px >= 8 * mpx && a.f == 16;
+    return supports_bank_bwd_in_mfma(a) && wide && many ? 3 : 2;
+}
 // mfma_walk_t64x16 where the 64 x 256 tiles are fewer than two per CU, else mfma_px_tail_t64x256 (16 x 512^2
 // pixels are 256 tiles: 125 against 160 us at r = 4; 8 x 1024^2 are 512: 245 against 236); block4_t64x256 above
 // 16 filters

@@ -1,0 +1,296 @@
+// Input gradient of the filter bank on the matrix cores, float32 operands carried exactly (radius 3 and 4, up to 16
+// filters), where the FMA tiles are bound by vector issue (F (2r+1)^2 FMAs per pixel).
+//
+//   z[u] = sum_f sum_k w[f,k] gy0[f, u - k],   gy0: gy extended by zero; the border pixels, onto which clamped
+//   positions fold, are rewritten by bank_bwd_edge.
+//
+// A wave owns 128 columns and walks down the rows of gy.  Row y reaches the 2r + 1 output rows y - r .. y + r: they
+// are the rows m of one product (v_mfma_f32_16x16x32_bf16)
+//   D[m][p] += sum_{t,f} A[m][(t,f)] B[(t,f)][p],   A[m][(t,f)] = w[f, u_m - y, r - t],
+//   B[(t,f)][p] = gy[f, y, x_p - r + t],            K = 2 taps x 16 filters, r + 1 pairs of taps,
+// where output row u sits in D's row u mod (2r + 1), so that finished rows leave and new ones enter without moving the
+// others: the tap operand rotates instead, read each row from a table in LDS with one row per w[., ky, .].  The 16
+// pixels of a product are 8 apart (x_p = x0 + 8 p + g, g = 0 .. 7 one accumulator each), so that the operand of
+// (g, pair t) depends on g + t alone: 8 + 2r loads of LDS serve 8 (r + 1) products, and a lane's 8 sums of a row are 8
+// consecutive pixels.  Rows of gy are loaded a row ahead, a lane having 4 pixels of 8 filters, and written to LDS as
+// records of one pixel's 8 filters; each wave has its own, so there is no barrier.  Two waves per SIMD: one wave alone
+// issues these products at half rate.
+//
+// Precision: v = v1 + v2 + v3 exactly, each part the bfloat16 nearest to what is left (8 significant bits and a sign
+// each, float32 has 24); products of parts are exact in float32.  v1 w1, v1 w2, v2 w1, v2 w2, v1 w3, v3 w1 are kept, what
+// is left out is below 2^-26 |v w|.  v1 w1 is summed apart from the smaller ones.
+// Infinite or NaN values turn every sum that meets them in a zero of A, or in the split, into a NaN: sums that are not
+// finite are taken again by FMAs, and so are those below 2^-96, where parts of the values may be subnormal bfloat16s.
+#include "icl_device.hpp"
+#include "icl_internal.hpp"
+#include "tile_stage.hpp"
+
+namespace icl {
+namespace {
+
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef float f8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+template <class P, class V>
+__device__ __forceinline__ P part(V& rest) {   // the leading bfloat16 of each element, taken off it
+    const P p = __builtin_convertvector(rest, P);
+    rest -= __builtin_convertvector(p, V);
+    return p;
+}
+
+constexpr int BM_COLS = 128;   // columns of a wave
+constexpr int BM_F = 16;       // filters of a product
+
+template <int R> struct BmLds {
+    static constexpr int N = 2 * R + 1, NJ = R + 1;
+    static constexpr int ROW = NJ * 64 + 32;        // table: bytes of one tap row (pair, quarter wave, 8 filters), padded
+    static constexpr int TAB = (N + 1) * ROW;       // and one row of zeros for D's unused rows
+    static constexpr int PHASE = 18 * 16;           // records of pixels 8 idx + phase, idx 0 .. 17
+    static constexpr int HALF = 8 * PHASE, PART = 2 * HALF, WAVE = 3 * PART;
+    static constexpr int BYTES = 3 * TAB + 4 * WAVE;
+};
+
+// z at one pixel by FMAs
+template <int R>
+__device__ __attribute__((noinline)) float bwd_in_pixel(const float* __restrict__ gyn, const float* __restrict__ w, int F,
+                                                        int H, int W, int x, int y) {
+    constexpr int N = 2 * R + 1;
+    float acc = 0.f;
+#pragma unroll 1
+    for (int f = 0; f < F; ++f)
+#pragma unroll 1
+        for (int j = 0; j < N; ++j) {
+            const int yy = y + R - j;
+            if (yy < 0 || yy >= H) continue;
+            const float* row = gyn + ((size_t)f * H + yy) * W;
+#pragma unroll 1
+            for (int i = 0; i < N; ++i) {
+                const int xx = x + R - i;
+                if (xx >= 0 && xx < W) acc = fmaf(w[((size_t)f * N + j) * N + i], row[xx], acc);
+            }
+        }
+    return acc;
+}
+
+template <int R>
+__global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __restrict__ gy, const float* __restrict__ w,
+                                                             float* __restrict__ gx, int F, int H, int W, int strips,
+                                                             int nblk, int th, int items,
+                                                             const float* __restrict__ scale) {
+    static_assert(R == 3 || R == 4, "the window starts on 3 or 4 columns left of the strip (fix4_clamped)");
+    using L = BmLds<R>;
+    constexpr int N = L::N, NJ = L::NJ;
+    __shared__ __attribute__((aligned(16))) char lds[L::BYTES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+
+    // the tap table: row j, pair jj, quarter q, filter i of a half: w[8 (q & 1) + i, j, 2 r - 2 jj - (q >> 1)]
+    for (int e = threadIdx.x; e < (N + 1) * NJ * 4; e += 256) {
+        const int j = e / (NJ * 4), jj = (e >> 2) % NJ, q = e & 3, t = 2 * jj + (q >> 1);
+        f8 v;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int f = 8 * (q & 1) + i;
+            v[i] = (j < N && t < N && f < F) ? w[((size_t)f * N + j) * N + 2 * R - t] : 0.f;
+        }
+        char* o = lds + j * L::ROW + jj * 64 + q * 16;
+        *reinterpret_cast<b8*>(o) = part<b8>(v);
+        *reinterpret_cast<b8*>(o + L::TAB) = part<b8>(v);
+        *reinterpret_cast<b8*>(o + 2 * L::TAB) = part<b8>(v);
+    }
+    char* rec = lds + 3 * L::TAB + wave * L::WAVE;
+    if (lane < 48) {   // the records past the last staged pixel (met by a zero tap only)
+        const v4f z = mk4(0.f, 0.f, 0.f, 0.f);
+        *reinterpret_cast<v4f*>(rec + lane * L::PHASE + 17 * 16) = z;
+    }
+    __syncthreads();
+    const int item = (int)blockIdx.x * 4 + wave;
+    if (item >= items) return;   // no barrier from here on
+    const int per = strips * nblk, n = item / per, rem = item - n * per, rb = rem / strips, strip = rem - rb * strips;
+    const int u0 = rb * th, u1 = min(H, u0 + th);
+    const int x0 = strip * BM_COLS, xs = x0 - R;
+    const float sc = scale ? *scale : 1.f;
+    const size_t hw = (size_t)H * W;
+    const float* gyn = gy + (size_t)n * F * hw;
+    float* gxn = gx + (size_t)n * hw;
+
+    // staging: a lane's 4 pixels from column cx of the 8 filters of half fh, and 2 filters of one of the 8 columns
+    // after those 128.  Filters past F read the last one (their taps are zero).
+    const int fh = lane >> 5, c4 = lane & 31, cx = xs + 4 * c4;
+    const int ex = xs + BM_COLS + (lane & 7), ef = 2 * (lane >> 3);
+    const bool edge = xs < 0 || xs + BM_COLS + 8 > W;
+    const float* p[8];
+    const float* pe[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = gyn + (size_t)min(8 * fh + i, F - 1) * hw + min(max(cx, 0), W - 4);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) pe[i] = gyn + (size_t)min(ef + i, F - 1) * hw + clampi(ex, W);
+    char* wr = rec + fh * L::HALF + 4 * (c4 & 1) * L::PHASE + (c4 >> 1) * 16;
+    char* we = rec + (lane >> 5) * L::HALF + (lane & 7) * L::PHASE + 16 * 16 + ((lane >> 3) & 3) * 4;
+    v4f v[8];
+    f2 ve;
+    auto fetch = [&](int y) __attribute__((always_inline)) {
+        const size_t o = (size_t)y * W;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const v4f_any*>(p[i] + o);
+        ve[0] = pe[0][o];
+        ve[1] = pe[1][o];
+    };
+    auto stage = [&]() __attribute__((always_inline)) {
+        if (edge) {   // gy is zero outside the image
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = outside4(fix4_clamped(v[i], W, cx), W, 1, cx, 0, 0.f);
+            if (ex >= W) ve[0] = ve[1] = 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            f8 a;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[i] = v[i][e];
+            *reinterpret_cast<b8*>(wr + e * L::PHASE) = part<b8>(a);
+            *reinterpret_cast<b8*>(wr + e * L::PHASE + L::PART) = part<b8>(a);
+            *reinterpret_cast<b8*>(wr + e * L::PHASE + 2 * L::PART) = __builtin_convertvector(a, b8);
+        }
+        *reinterpret_cast<b2*>(we) = part<b2>(ve);
+        *reinterpret_cast<b2*>(we + L::PART) = part<b2>(ve);
+        *reinterpret_cast<b2*>(we + 2 * L::PART) = __builtin_convertvector(ve, b2);
+    };
+
+    const int m = lane & 15, q = lane >> 4, par = q >> 1;
+    v4f hi[8], lo[8];   // v1 w1, and the smaller products
+#pragma unroll
+    for (int g = 0; g < 8; ++g) hi[g] = lo[g] = mk4(0.f, 0.f, 0.f, 0.f);
+    const char* rd = rec + (q & 1) * L::HALF + m * 16;
+    const char* rda = rd + par * L::PHASE;                          // pixel 8 p + s + par, s & 7 < 7
+    const char* rdb = rd + par * (16 - 7 * L::PHASE);               // s & 7 = 7: par steps into the next record
+
+    // b: D's row of output row y - r
+    auto products = [&](int b) __attribute__((always_inline)) {
+        const int j = m < N ? (m >= b ? m - b : m - b + N) : N;
+        const char* ta = lds + j * L::ROW + q * 16;
+        b8 a[3][NJ];
+#pragma unroll
+        for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) a[k][jj] = *reinterpret_cast<const b8*>(ta + k * L::TAB + jj * 64);
+        b8 x[2][2][3];   // the operands of s = 2 i, 2 i + 1 and of the next two, whose loads run under these products
+        auto operands = [&](auto i_c) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_c)::value;
+            static_for<2>([&](auto o_c) __attribute__((always_inline)) {
+                constexpr int o = decltype(o_c)::value, s = 2 * i + o;
+                const char* r = ((s & 7) == 7 ? rdb : rda) + (s & 7) * L::PHASE + (s >> 3) * 16;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) x[i & 1][o][k] = *reinterpret_cast<const b8*>(r + k * L::PART);
+            });
+        };
+        operands(std::integral_constant<int, 0>{});
+        static_for<4 + R>([&](auto i_c) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_c)::value;
+            if constexpr (i + 1 < 4 + R) operands(std::integral_constant<int, i + 1>{});
+            __builtin_amdgcn_sched_barrier(0);
+#define ICL_BM_PRODUCT(ACC, KA, KX)                                                                                      \
+    _Pragma("unroll") for (int o = 0; o < 2; ++o) _Pragma("unroll") for (int jj = 0; jj < NJ; ++jj) {                    \
+        const int g = 2 * (i - jj) + o;                                                                                  \
+        if (g >= 0 && g < 8)                                                                                             \
+            ACC[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[KA][jj], x[i & 1][o][KX], ACC[g], 0, 0, 0);               \
+    }
+            ICL_BM_PRODUCT(lo, 2, 0)
+            ICL_BM_PRODUCT(hi, 0, 0)
+            ICL_BM_PRODUCT(lo, 1, 0)
+            ICL_BM_PRODUCT(lo, 1, 1)
+            ICL_BM_PRODUCT(lo, 0, 1)
+            ICL_BM_PRODUCT(lo, 0, 2)
+#undef ICL_BM_PRODUCT
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // output row u, complete in D's row b: the quarter of the wave that holds it writes 8 pixels per lane and clears it
+    auto emit = [&](int u, int b, bool write) __attribute__((always_inline)) {
+        float o[8];
+        const bool mine = q == (b >> 2);
+        static_for<4>([&](auto r_c) __attribute__((always_inline)) {
+            constexpr int r = decltype(r_c)::value;
+            if ((b & 3) == r) {
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    o[g] = hi[g][r] + lo[g][r];
+                    hi[g][r] = mine ? 0.f : hi[g][r];
+                    lo[g][r] = mine ? 0.f : lo[g][r];
+                }
+            }
+        });
+        if (!write || !mine) return;
+        const int x = x0 + 8 * m;
+        auto exact = [](float s) { return s == 0.f || (fabsf(s) >= 0x1p-96f && fabsf(s) < __builtin_inff()); };
+        float big = 0.f, small = __builtin_inff();   // a NaN or an infinity stays in the sum
+#pragma unroll
+        for (int g = 0; g < 8; ++g) big += fabsf(o[g]), small = fminf(small, fabsf(o[g]));
+        if (!(big < __builtin_inff() && small >= 0x1p-96f)) {
+#pragma unroll
+            for (int g = 0; g < 8; ++g)
+                if (x + g < W && !exact(o[g])) o[g] = bwd_in_pixel<R>(gyn, w, F, H, W, x + g, u);
+        }
+        float* out = gxn + (size_t)u * W + x;
+        if (x + 8 <= W) {
+            *reinterpret_cast<v4f_any*>(out) = sc * mk4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<v4f_any*>(out + 4) = sc * mk4(o[4], o[5], o[6], o[7]);
+        } else {
+#pragma unroll
+            for (int g = 0; g < 8; ++g)
+                if (x + g < W) out[g] = sc * o[g];
+        }
+    };
+
+    const int ya = max(0, u0 - R), yb = min(H - 1, u1 - 1 + R);
+    int b = (ya - R - u0 + 2 * N) % N, bp = 0;
+    fetch(ya);
+    for (int y = ya;; ++y) {
+        const int u = y - 1 - R;   // the row that the step before completed
+        if (y <= yb) stage();
+        if (y > ya) emit(u, bp, u >= u0);
+        if (u >= u1 - 1) break;
+        if (y <= yb) {
+            fetch(min(y + 1, yb));
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            products(b);
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        bp = b;
+        b = b + 1 == N ? 0 : b + 1;
+    }
+}
+
+template <int R>
+hipError_t launch_R(const BankArgs& a) {
+    const int strips = (a.w + BM_COLS - 1) / BM_COLS;
+    const long long per = (long long)a.n * strips;
+    // rows per wave: the split into row blocks whose rounds of 2048 resident waves walk the fewest rows
+    const int most = (a.h + 15) / 16;
+    int nblk = 1;
+    long long best = -1;
+    for (int k = 1; k <= most && k <= 256; ++k) {
+        const int th = (a.h + k - 1) / k;
+        const long long rounds = (per * k + 2047) / 2048, cost = rounds * (th + 2 * R);
+        if (best < 0 || cost < best) best = cost, nblk = k;
+        if (rounds > 16) break;
+    }
+    const int th = (a.h + nblk - 1) / nblk;
+    nblk = (a.h + th - 1) / th;
+    const long long items = per * nblk;
+    if (items > 0x7ffffff0LL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(bank_bwd_in_mfma_k<R>, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, a.st, a.a, a.b, a.out, a.f,
+                       a.h, a.w, strips, nblk, th, (int)items, a.scale);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool supports_bank_bwd_in_mfma(const BankArgs& a) { return (a.r == 3 || a.r == 4) && a.f <= BM_F && a.w >= 8; }
+
+// every pixel but the folds at the border
+hipError_t launch_bank_bwd_in_mfma(const BankArgs& a) { return a.r == 3 ? launch_R<3>(a) : launch_R<4>(a); }
+
+}  // namespace icl

@@ -85,6 +85,10 @@ struct BankArgs {
     const float* scale = nullptr;   // adjoints: device factor on the output (null = 1)
 };
 
+// the input gradient but for the folds at the border, on the matrix cores
+bool supports_bank_bwd_in_mfma(const BankArgs& a);
+hipError_t launch_bank_bwd_in_mfma(const BankArgs& a);
+
 struct BankSseArgs {
     const float *x, *w, *t;
     float *y, *gy, *loss;   // y and gy may be null
