@@ -13,8 +13,13 @@
 // pixels of a product are 8 apart (x_p = x0 + 8 p + g, g = 0 .. 7 one accumulator each), so that the operand of
 // (g, pair t) depends on g + t alone: 8 + 2r loads of LDS serve 8 (r + 1) products, and a lane's 8 sums of a row are 8
 // consecutive pixels.  Rows of gy are loaded a row ahead, a lane having 4 pixels of 8 filters, and written to LDS as
-// records of one pixel's 8 filters; each wave has its own, so there is no barrier.  Two waves per SIMD: one wave alone
-// issues these products at half rate.
+// records of one pixel's 8 filters; each wave has its own, so there is no barrier.
+//
+// Bound by the matrix cores: 32 x 16 x 1024^2, r = 4, takes 1.09e15 operations of them (9 of 16 rows of D and 9 of 10
+// taps of the pairs are of use, six products per pair of operands) in 0.86 ms = 1.27 PFLOP/s, with 2.3 GB of gy read
+// meanwhile; the FMA tiles took 1.11 ms.  Two waves per SIMD (one alone issues these products at half rate); the operands
+// of the next products are loaded under these (0.84 against 0.86 without).  The split of the next row between the
+// products instead of between the rows spilled and was slower (0.90).
 //
 // Precision: v = v1 + v2 + v3 exactly, each part the bfloat16 nearest to what is left (8 significant bits and a sign
 // each, float32 has 24); products of parts are exact in float32.  v1 w1, v1 w2, v2 w1, v2 w2, v1 w3, v3 w1 are kept, what
