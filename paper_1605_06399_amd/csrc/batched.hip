@@ -145,12 +145,12 @@ struct ColRanges {
     int end[RMAX + 1];
 };
 
-// The register budget is set for the work-groups the LDS admits: four per CU for 64-column
-// strips with 64-row steps (40 KB), three for 128-column strips with 32-row steps (42 KB).
+// Three work-groups per CU: four of the 64-column strips' LDS (40 KB) fit, but with the edge strips' loads in vectors
+// too their 128 registers spill (256 images, float16, segments of 256 rows: 433 us, three 363; before, with an edge strip's
+// pixels read one by one and four groups, 431).
 template <class T, int CX, int STEP>
-__global__ __launch_bounds__(256, CX == 1 ? 4 : 3) void sep_batched_col_k(const DevImage* __restrict__ imgs,
-                                                                         const ColItem* __restrict__ items,
-                                                                         ColRanges rg) {
+__global__ __launch_bounds__(256, 3) void sep_batched_col_k(const DevImage* __restrict__ imgs,
+                                                            const ColItem* __restrict__ items, ColRanges rg) {
     using G = ColGeom<CX, STEP>;
     __shared__ __attribute__((aligned(16))) float in_s[G::IN_FLOATS];
     __shared__ __attribute__((aligned(16))) float t_s[G::T_FLOATS];
@@ -272,8 +272,14 @@ Problem plan_problem(const icl_batch_plan* p) {
                    std::max(p->nimg, 1)};
 }
 
-// the first column walk where it can address every image, else the tile walk
-int plan_default(const icl_batch_plan* p) { return p->col_ok ? kFirstCol : batched_default(); }
+// The column walk over segments of 256 rows where it can address every image, of 64 rows for batches of less than
+// 4096 tiles of 64 x 64 (a segment is one work-group's serial walk, and there are 768 work-groups); else the tile walk.
+// us, segments of 256 / 128 / 64 rows, tile walk: 256 images of 64 .. 2048, float16 363 / 385 / 432, 541; 30 of them
+// (8000 tiles) 50 / 52 / 55, 66; 100 images of 64 .. 400, bfloat16 (1600) 23 / 24 / 22, 23; 16 of 64 .. 1000 (1100)
+// 20 / 15 / 14, 16; 8 of 64 .. 256 18 / 12 / 7, 7.
+int plan_default(const icl_batch_plan* p) {
+    return !p->col_ok ? batched_default() : p->ntiles[0] < 4096 ? kFirstCol + 4 : kFirstCol;
+}
 
 int plan_variant(const icl_batch_plan* p) {
     int v = (variant_forced(ICL_OP_CONV_SEP_BATCHED) || p->tuned < 0) ? select_variant(plan_problem(p), plan_default(p))

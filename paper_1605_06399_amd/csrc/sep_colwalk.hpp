@@ -41,65 +41,52 @@ template <int CX, int STEP> struct ColGeom {
     static constexpr int T_FLOATS = (STEP + 2 * COL_RMAX) * CW;
 };
 
-template <class T, int R, int NROWS, int CX = 1>
+// INSIDE: the staged columns lie in the image and its rows are 4-pixel aligned.
+template <class T, int R, int NROWS, int CX, bool INSIDE>
 struct ColStage {
     static constexpr int RA = (R + 3) & ~3, LW = 64 * CX + 2 * RA, C4 = LW / 4;
     static constexpr int NCH = NROWS * C4, PER = (NCH + 255) / 256;
     typename Raw4<T>::type v[PER > 0 ? PER : 1];
     int gy = 0;
 
-    // Staged rows gy .. gy + NROWS - 1 (read clamped into the image), columns x0 - RA .. x0 + 64 CX - 1 + RA.
-    // inside (the columns lie in the image, rows 4-pixel aligned): straight vector loads into
-    // registers, all in flight together, written to LDS by store().  Otherwise nothing is
-    // loaded here: store() reads the chunks through the clamp itself (a strip at an image's
-    // left or right edge, one in about eight), which keeps the rare edge path out of the
-    // register budget of the prefetch.
-    __device__ __forceinline__ void load(const DevImage& d, Rsrc rs, int x0, int row0, bool inside) {
+    // Staged rows gy .. gy + NROWS - 1 (read clamped into the image), columns x0 - RA .. x0 + 64 CX - 1 + RA: vector
+    // loads into registers, all in flight together, written to LDS by store().  Strips inside an image read through the
+    // buffer; the others (at its left and right edge, one in eight, and rows off 4 pixels) four pixels at any address from
+    // the nearest column that has four, put in place by store().
+    __device__ __forceinline__ void load(const DevImage& d, Rsrc rs, int x0, int row0) {
         gy = row0;
-        if (!inside) return;
+        typedef typename Raw4<T>::type raw_any __attribute__((aligned(T::size)));
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int idx = (int)threadIdx.x + 256 * k;
             if (NCH % 256 != 0 && idx >= NCH) break;
-            const int rr = idx / C4, c4 = idx - rr * C4;
+            const int rr = idx / C4, c4 = idx - rr * C4, x = x0 - RA + 4 * c4;
             const unsigned row = (unsigned)clampi(gy + rr, d.H) * (unsigned)d.sp;
-            v[k] = bload4_raw<T>(rs, row + (unsigned)(x0 - RA + 4 * c4) * T::size);
-        }
-    }
-    // bd: the boundary; with a constant, a staged pixel outside the image is the constant
-    __device__ __forceinline__ void store(float* __restrict__ in_s, const DevImage& d, Rsrc rs, int x0, bool inside,
-                                          Border bd) const {
-        if (inside) {
-#pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int idx = (int)threadIdx.x + 256 * k;
-                if (NCH % 256 != 0 && idx >= NCH) break;
-                const int rr = idx / C4, c4 = idx - rr * C4;
-                v4f e = decode4<T>(v[k]);
-                if (bd.constant && (gy + rr < 0 || gy + rr >= d.H)) e = mk4(bd.value, bd.value, bd.value, bd.value);
-                lds4(&in_s[rr * LW + 4 * c4], e);
-            }
-            return;
-        }
-        for (int idx = (int)threadIdx.x; idx < NCH; idx += 256) {
-            const int rr = idx / C4, c4 = idx - rr * C4;
-            const unsigned row = (unsigned)clampi(gy + rr, d.H) * (unsigned)d.sp;
-            const int x = x0 - RA + 4 * c4;
-            typename Raw4<T>::type r;
-            if (d.vec_ok && x >= 0 && x + 4 <= d.W) {
-                r = bload4_raw<T>(rs, row + (unsigned)x * T::size);
+            if (INSIDE) {
+                v[k] = bload4_raw<T>(rs, row + (unsigned)x * T::size);
+            } else if (d.W >= 4) {
+                v[k] = *reinterpret_cast<const raw_any*>(static_cast<const char*>(d.src) + row +
+                                                         (unsigned)min(max(x, 0), d.W - 4) * T::size);
             } else {
                 unsigned e[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) e[q] = bload1_raw<T>(rs, row + (unsigned)clampi(x + q, d.W) * T::size);
-                r = pack4_raw<T>(e[0], e[1], e[2], e[3]);
+                v[k] = pack4_raw<T>(e[0], e[1], e[2], e[3]);
             }
-            v4f e = decode4<T>(r);
-            if (bd.constant) {
-                const bool yout = gy + rr < 0 || gy + rr >= d.H;
+        }
+    }
+    // bd: the boundary; with a constant, a staged pixel outside the image is the constant
+    __device__ __forceinline__ void store(float* __restrict__ in_s, const DevImage& d, int x0, Border bd) const {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (yout || x + q < 0 || x + q >= d.W) e[q] = bd.value;
+        for (int k = 0; k < PER; ++k) {
+            const int idx = (int)threadIdx.x + 256 * k;
+            if (NCH % 256 != 0 && idx >= NCH) break;
+            const int rr = idx / C4, c4 = idx - rr * C4, x = x0 - RA + 4 * c4;
+            v4f e = decode4<T>(v[k]);
+            if (!INSIDE) e = fix4_clamped(e, d.W, x);
+            if (bd.constant) {
+                if (!INSIDE) e = outside4(e, d.W, d.H, x, gy + rr, bd.value);
+                else if (gy + rr < 0 || gy + rr >= d.H) e = mk4(bd.value, bd.value, bd.value, bd.value);
             }
             lds4(&in_s[rr * LW + 4 * c4], e);
         }
@@ -129,10 +116,10 @@ __device__ __forceinline__ DevImage uni(const DevImage& d) {
     return u;
 }
 
-template <class T, int R, int CX = 1, int STEP = 64>
-__device__ __forceinline__ void col_item(const DevImage& d, const ColItem& it, float* __restrict__ in_s,
-                                         float* __restrict__ t_s, Border bd = {}) {
-    constexpr int RA = (R + 3) & ~3, CW = 64 * CX;
+template <class T, int R, int CX, int STEP, bool INSIDE>
+__device__ __forceinline__ void col_walk(const DevImage& d, const ColItem& it, float* __restrict__ in_s,
+                                         float* __restrict__ t_s, Border bd) {
+    constexpr int CW = 64 * CX;
     const Rsrc rs = make_rsrc(d.src, d.src_bytes);
     float tx[2 * R + 1], ty[2 * R + 1];
 #pragma unroll
@@ -140,33 +127,42 @@ __device__ __forceinline__ void col_item(const DevImage& d, const ColItem& it, f
         tx[i] = uni(d.tx[i]);
         ty[i] = uni(d.ty[i]);
     }
-    const bool inside = d.vec_ok && it.x0 - RA >= 0 && it.x0 + CW + RA <= d.W;
     const int nsteps = (it.rows + STEP - 1) / STEP;
     // prologue: T rows 0 .. 2r - 1 from input rows y0 - r .. y0 + r - 1
-    ColStage<T, R, STEP, CX> st;
+    ColStage<T, R, STEP, CX, INSIDE> st;
     if constexpr (R > 0) {
-        ColStage<T, R, 2 * R, CX> pro;
-        pro.load(d, rs, it.x0, it.y0 - R, inside);
-        st.load(d, rs, it.x0, it.y0 + R, inside);
-        pro.store(in_s, d, rs, it.x0, inside, bd);
+        ColStage<T, R, 2 * R, CX, INSIDE> pro;
+        pro.load(d, rs, it.x0, it.y0 - R);
+        st.load(d, rs, it.x0, it.y0 + R);
+        pro.store(in_s, d, it.x0, bd);
         __syncthreads();
         sep_row_pass<R, 0, CX, 1>(in_s, t_s, tx);
         __syncthreads();
     } else {
-        st.load(d, rs, it.x0, it.y0 + R, inside);
+        st.load(d, rs, it.x0, it.y0 + R);
     }
     for (int s = 0; s < nsteps; ++s) {
-        st.store(in_s, d, rs, it.x0, inside, bd);
+        st.store(in_s, d, it.x0, bd);
         if (R > 0 && s > 0) {   // the previous step's last 2r T rows become the first
             for (int q = (int)threadIdx.x; q < 2 * R * CW / 4; q += 256) lds4(&t_s[4 * q], lds4(&t_s[STEP * CW + 4 * q]));
         }
         __syncthreads();
-        if (s + 1 < nsteps) st.load(d, rs, it.x0, it.y0 + STEP * (s + 1) + R, inside);
+        if (s + 1 < nsteps) st.load(d, rs, it.x0, it.y0 + STEP * (s + 1) + R);
         sep_row_pass<R, STEP - 2 * R, CX, 1>(in_s, t_s + 2 * R * CW, tx);
         __syncthreads();
         sep_col_pass<T, R, STEP, CX, 6>(t_s, d.dst, d.dp, d.W, d.H, ty, it.x0, it.y0 + STEP * s);
         __syncthreads();
     }
+}
+
+// Two bodies, as one holds the registers of both kinds of load (256 images, float16: 434 -> 499 us).  An edge strip's
+// pixels read one by one at the store, instead, made its walk several times as long as the others (434; now 363).
+template <class T, int R, int CX = 1, int STEP = 64>
+__device__ __forceinline__ void col_item(const DevImage& d, const ColItem& it, float* __restrict__ in_s,
+                                         float* __restrict__ t_s, Border bd = {}) {
+    constexpr int RA = (R + 3) & ~3;
+    if (d.vec_ok && it.x0 - RA >= 0 && it.x0 + 64 * CX + RA <= d.W) col_walk<T, R, CX, STEP, true>(d, it, in_s, t_s, bd);
+    else col_walk<T, R, CX, STEP, false>(d, it, in_s, t_s, bd);
 }
 
 }  // namespace icl
