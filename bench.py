@@ -201,7 +201,7 @@ def write_traffic(fetch_csv, write_csv, side=4096):
 
 # Kernels of the extra workloads whose HBM traffic is summarised: (workload, symbol pattern, label,
 # source files, algorithmic bytes per launch).  The symbols are those of the workloads' main launches
-# (the border-band launches of corners and NMS are listed by the summary as they are).
+# (the border-band launches of the NMS strips are listed by the summary as they are).
 _B_PX = 273398743          # pixels of the 256-image uneven batch (seeded recipe)
 _BANK = (32, 16, 1024 * 1024)
 WORKLOAD_KERNELS = [
@@ -211,24 +211,25 @@ WORKLOAD_KERNELS = [
      "icl_device.hpp"], 4 * _B_PX),
     ("batch", r"sep_batched_col_k<icl::(F16|BF16), (\d), (\d+)>", "colwalk_cx{1}_step{2}_{0}",
      ["batched.hip", "sep_colwalk.hpp", "sep_tile.hpp", "tile_stage.hpp", "icl_device.hpp"], 4 * _B_PX),
-    ("corner", r"harris_(fused|stream)<(\d+), (\d+)>", "harris_{0}_t{2}", ["harris.hip", "harris_strip.hpp",
+    ("corner", r"harris_(fused|strips)<(\d+), (\d+)(?:, (?:true|false))?>", "harris_{0}_t{2}", ["harris.hip", "harris_strip.hpp",
      "icl_device.hpp"], 8 * 8192 * 8192),
     ("corner", r"nms_stream<(\d+)>", "nms_stream_t{0}", ["nms.hip", "harris_strip.hpp", "icl_device.hpp"],
      5 * 8192 * 8192),
     ("corner", r"nms_stream_a<(\d+), (true|false)>", "nms_stream_a_t{0}_sm:{1}", ["nms.hip", "harris_strip.hpp",
      "icl_device.hpp"], 5 * 8192 * 8192),
-    ("corner", r"corners_stream<(\d+), (\d+), 1>", "corners_stream_t{1}", ["corners.hip", "harris_strip.hpp",
+    ("corner", r"corners_stream<(\d+), (\d+)>", "corners_stream_t{1}", ["corners.hip", "harris_strip.hpp",
      "icl_device.hpp"], 5 * 8192 * 8192),
     ("bank", r"bank_fwd_(mfma_k<4, true, \d+, (?:true|false)>|pers_k<4, true>|sse_tpre_k<4>)", "fwd_sse:{0}",
      ["bank.hip"],
      4 * (_BANK[0] * _BANK[2] + 2 * _BANK[0] * _BANK[1] * _BANK[2])),
-    ("bank", r"bank_bwd_in_(mfma_k|pers_k|k)<4>", "bwd_input:{0}", ["bank.hip"],
+    ("bank", r"bank_bwd_in_(mfma_k|pers_k|k)<4>", "bwd_input:{0}", ["bank.hip", "bank_bwd_in_mfma.hip"],
      4 * (_BANK[0] * _BANK[1] * _BANK[2] + _BANK[0] * _BANK[2])),
     ("bank", r"bank_bwd_(wm_k<4, \d, (?:true|false)(?:, (?:true|false))?>|w4_k<4, \d, 16>)", "bwd_filter:{0}",
      ["bank.hip"],
      4 * (_BANK[0] * _BANK[1] * _BANK[2] + _BANK[0] * _BANK[2])),
     ("paper", r"sep_(fused|pers)<icl::F32, 2, (\d+), (\d+)>", "sep5_constant:{0}_t{1}_c{2}",
      KERNEL_SOURCES["sep"], 8 * 4096 * 4096),
+    ("paper", r"conv2d_u8_mfma_k<2>", "u8_5x5:mfma_i8", ["conv2d_u8_mfma.hip", "icl_device.hpp"], 2 * 8192 * 8192),
     ("paper", r"u8_strip<2, (\d+), (\d+), (\d+)>", "u8_5x5:strip_p{1}_t{0}_q{2}", ["conv2d_u8.hip", "icl_device.hpp"],
      2 * 8192 * 8192),
     ("volume", r"sep3_stream<icl::F32, (\d+), (\d+)>", "sep3d_r{0}:stream_z{1}", ["conv3d.hip", "icl_device.hpp"],
@@ -415,8 +416,8 @@ SQ_RUNS = {"sweep": "--steps 3 --warmup 1 --no-extras --no-cpu", "bank": "--only
            "batch": "--only batch --steps 4 --warmup 1 --no-cpu", "corner": "--only corner --steps 4 --warmup 1 --no-cpu",
            "paper": "--only paper --steps 4 --warmup 1 --no-cpu"}
 SQ_KERNELS = (r"conv2d_pers<F32, [1-7], ", r"sep_(fused|pers)<F32, [1-7], ", r"bank_(fwd_mfma_k<4, true, 0, true>|"
-              r"bwd_in_pers_k<4>|bwd_wm_k<4, 4, true, (?:true|false)>)", r"sep_batched_col_k<F16, 1, 64>", r"harris_stream<2, 16>",
-              r"nms_stream_a<4, false>", r"corners_stream<2, 12, 1>", r"u8_strip<2, \d+, \d+, \d+>")
+              r"bwd_in_(?:pers|mfma)_k<4>|bwd_wm_k<4, 4, true, (?:true|false)>)", r"sep_batched_col_k<F16, 1, 64>", r"harris_strips<2, 16, false>",
+              r"nms_stream_a<4, false>", r"corners_stream<2, 32>", r"conv2d_u8_mfma_k<2>", r"u8_strip<2, \d+, \d+, \d+>")
 
 
 def write_counter_summary(dirs, out_dir=None):
