@@ -24,6 +24,7 @@
 // (52 us): they read past the row's ends and mask, and only the image's first and last rows shift bytes.
 #include "icl_device.hpp"
 #include "icl_internal.hpp"
+#include "u8_rows.hpp"
 
 namespace icl {
 namespace {
@@ -32,7 +33,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef v4i v4i_any __attribute__((aligned(1)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
 
-constexpr int UW = 256;       // output columns of a wave
+constexpr int UW = U8_COLS;   // output columns of a wave
 constexpr int UT = 14;        // words of a padded tap row
 constexpr int uq(int r, bool inside) { return inside ? (r == 2 ? 6 : 8) : r == 2 ? 2 : 4; }   // input rows in flight
 constexpr int waves_per_simd(int r) { return r <= 2 ? 4 : r == 3 ? 3 : 2; }   // the register budget
@@ -66,21 +67,21 @@ __device__ __forceinline__ v4i bytes_fix(v4i v, int c, int cb, uint32_t fill) {
 template <int R, bool EXTRA, bool INSIDE>
 __device__ __forceinline__ void u8_walk(const uint8_t* __restrict__ src, size_t sp, uint8_t* __restrict__ dst, size_t dp,
                                         int W, int H, const uint32_t (*__restrict__ wl)[2 * R + 2][UT], int tsum, int shift,
-                                        int bias, int cmode, int cval, int xs, int y0, int rows) {
+                                        int bias, int cmode, int cval, int tail, int xs, int y0, int rows) {
     constexpr int NP = R + 1, PARTS = EXTRA ? 3 : 2;
     const int lane = (int)threadIdx.x & 63, n = lane & 15, g = lane >> 4, half = g >> 1;
     const int K = rows + 2 * R;
-    const int c = xs - 8 + 16 * n + 16 * (g & 1), cb = min(max(c, 0), W - 16);
+    const int c = u8_col(xs, n, g), cb = min(max(c, 0), W - 16);
     const unsigned rowoff = half ? (unsigned)sp : 0u;
-    // Rows whose columns left of 0 or right of W - 1 could lie outside the image's memory (its first and last):
-    // an edge strip reads those from clamped columns, all others straight, into the padding or the neighbour row.
-    auto guarded = [&](int k) { return y0 - R + k <= 0 || y0 - R + k + 1 >= H - 1; };
+    // Rows whose columns left of 0 or right of W - 1 could lie outside the image's memory (its first row and its last
+    // ones): an edge strip reads those from clamped columns, all others straight, into the padding or neighbour rows.
+    auto guarded = [&](int k) { return !u8_straight(y0 - R + k, H, tail); };
     auto load_row = [&](int k) -> v4i {   // row pair y0 - R + k, read clamped: this lane's row of it
         const int q = y0 - R + k;
-        const uint8_t* row = src + (size_t)clampi(q, H) * sp;
+        const uint8_t* row = src + (size_t)u8_row(q, H) * sp;
         const unsigned off = q >= 0 && q + 1 < H ? rowoff : 0u;
         if constexpr (INSIDE) return *reinterpret_cast<const v4i_any*>(row + (off + (unsigned)c));
-        return *reinterpret_cast<const v4i_any*>(row + ((ptrdiff_t)off + c + (-(int)guarded(k) & (cb - c))));
+        return *reinterpret_cast<const v4i_any*>(row + u8_lane(q, H, tail, rowoff, c, cb));
     };
     const int ce = c < 0 ? 0 : W - 1;   // the column that stands for those outside
     auto load_end = [&](int k) -> uint32_t {
@@ -195,7 +196,7 @@ template <int R>
 __global__ __launch_bounds__(256, waves_per_simd(R)) void conv2d_u8_mfma_k(const uint8_t* __restrict__ src, size_t sp,
                                                         uint8_t* __restrict__ dst, size_t dp, int W, int H,
                                                         const int16_t* __restrict__ taps, int shift, int nstrips,
-                                                        int nitems, int TH, int words, int cmode, int cval) {
+                                                        int nitems, int TH, int words, int tail, int cmode, int cval) {
     constexpr int N = 2 * R + 1;
     // the taps' low, high and extra parts as bytes at 24 - r .. 24 + r of each row, zeros around; row N is zero
     __shared__ uint32_t wl[3][N + 1][UT];
@@ -219,11 +220,11 @@ __global__ __launch_bounds__(256, waves_per_simd(R)) void conv2d_u8_mfma_k(const
     const int seg = item / nstrips, xs = (item - seg * nstrips) * UW, y0 = seg * TH;
     const int bias = shift > 0 ? 1 << (shift - 1) : 0, rows = min(TH, H - y0);
     if (__builtin_amdgcn_readfirstlane(sums[1]))
-        u8_walk<R, true, false>(src, sp, dst, dp, W, H, wl, tsum, shift, bias, cmode, cval, xs, y0, rows);
-    else if (words && xs >= 8 && xs + UW + 8 <= W)
-        u8_walk<R, false, true>(src, sp, dst, dp, W, H, wl, tsum, shift, bias, cmode, cval, xs, y0, rows);
+        u8_walk<R, true, false>(src, sp, dst, dp, W, H, wl, tsum, shift, bias, cmode, cval, tail, xs, y0, rows);
+    else if (words && u8_inside(xs, W))
+        u8_walk<R, false, true>(src, sp, dst, dp, W, H, wl, tsum, shift, bias, cmode, cval, tail, xs, y0, rows);
     else
-        u8_walk<R, false, false>(src, sp, dst, dp, W, H, wl, tsum, shift, bias, cmode, cval, xs, y0, rows);
+        u8_walk<R, false, false>(src, sp, dst, dp, W, H, wl, tsum, shift, bias, cmode, cval, tail, xs, y0, rows);
 }
 
 template <int R>
@@ -238,7 +239,8 @@ hipError_t launch_R(const U8Args& a) {
     // buffer stores of whole words: the destination's rows start on one
     const int words = (uintptr_t)a.dst % 4 == 0 && a.dp % 4 == 0;
     hipLaunchKernelGGL(conv2d_u8_mfma_k<R>, dim3(grid_pad8((items + 3) / 4)), dim3(256), 0, a.st, a.src, a.sp, a.dst,
-                       a.dp, a.W, a.H, a.taps, a.shift, nstrips, (int)items, th, words, a.cmode, a.cval);
+                       a.dp, a.W, a.H, a.taps, a.shift, nstrips, (int)items, th, words,
+                       u8_tail_rows(a.W, (unsigned)a.sp), a.cmode, a.cval);
     return hipGetLastError();
 }
 
