@@ -24,8 +24,12 @@
 // Precision: v = v1 + v2 + v3 exactly, each part the bfloat16 nearest to what is left (8 significant bits and a sign
 // each, float32 has 24); products of parts are exact in float32.  v1 w1, v1 w2, v2 w1, v2 w2, v1 w3, v3 w1 are kept, what
 // is left out is below 2^-26 |v w|.  v1 w1 is summed apart from the smaller ones.
-// Infinite or NaN values turn every sum that meets them in a zero of A, or in the split, into a NaN: sums that are not
-// finite are taken again by FMAs, and so are those below 2^-96, where parts of the values may be subnormal bfloat16s.
+// gy and w are split after a scaling by 2^24, which is exact, and the sums scaled back: the last bit of the smallest
+// float32 (2^-149) is then a normal bfloat16, so that no operand below 2^104 loses bits in its split (unscaled, one below
+// 2^-110 did: gy 1e-37 under taps of 1e12 erred by 3e-4 of the result, float32 FMAs by 7e-7).  The scaling costs a
+// multiplication per staged value and no time that can be measured.
+// Infinite, NaN or overflowing values turn every sum that meets them in a zero of A, or in the split, into a NaN, and
+// scaled sums from 2^80 on are infinite: sums that are not finite are taken again by FMAs.
 #include "icl_device.hpp"
 #include "icl_internal.hpp"
 #include "tile_stage.hpp"
@@ -46,6 +50,7 @@ __device__ __forceinline__ P part(V& rest) {   // the leading bfloat16 of each e
 }
 
 constexpr int BM_COLS = 128;   // columns of a wave
+constexpr float BM_UP = 0x1p24f, BM_DOWN = 0x1p-48f;   // the operands' scale, and the sums' back
 constexpr int BM_F = 16;       // filters of a product
 
 template <int R> struct BmLds {
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int f = 8 * (q & 1) + i;
-            v[i] = (j < N && t < N && f < F) ? w[((size_t)f * N + j) * N + 2 * R - t] : 0.f;
+            v[i] = (j < N && t < N && f < F) ? BM_UP * w[((size_t)f * N + j) * N + 2 * R - t] : 0.f;
         }
         char* o = lds + j * L::ROW + jj * 64 + q * 16;
         *reinterpret_cast<b8*>(o) = part<b8>(v);
@@ -152,11 +157,12 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
         for (int e = 0; e < 4; ++e) {
             f8 a;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = v[i][e];
+            for (int i = 0; i < 8; ++i) a[i] = BM_UP * v[i][e];
             *reinterpret_cast<b8*>(wr + e * L::PHASE) = part<b8>(a);
             *reinterpret_cast<b8*>(wr + e * L::PHASE + L::PART) = part<b8>(a);
             *reinterpret_cast<b8*>(wr + e * L::PHASE + 2 * L::PART) = __builtin_convertvector(a, b8);
         }
+        ve *= BM_UP;
         *reinterpret_cast<b2*>(we) = part<b2>(ve);
         *reinterpret_cast<b2*>(we + L::PART) = part<b2>(ve);
         *reinterpret_cast<b2*>(we + 2 * L::PART) = __builtin_convertvector(ve, b2);
@@ -227,14 +233,13 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
         });
         if (!write || !mine) return;
         const int x = x0 + 8 * m;
-        auto exact = [](float s) { return s == 0.f || (fabsf(s) >= 0x1p-96f && fabsf(s) < __builtin_inff()); };
-        float big = 0.f, small = __builtin_inff();   // a NaN or an infinity stays in the sum
+        float big = 0.f;   // a NaN or an infinity stays in the sum
 #pragma unroll
-        for (int g = 0; g < 8; ++g) big += fabsf(o[g]), small = fminf(small, fabsf(o[g]));
-        if (!(big < __builtin_inff() && small >= 0x1p-96f)) {
+        for (int g = 0; g < 8; ++g) big += fabsf(o[g]), o[g] *= BM_DOWN;
+        if (!(big < __builtin_inff())) {
 #pragma unroll
             for (int g = 0; g < 8; ++g)
-                if (x + g < W && !exact(o[g])) o[g] = bwd_in_pixel<R>(gyn, w, F, H, W, x + g, u);
+                if (x + g < W && !(fabsf(o[g]) < __builtin_inff())) o[g] = bwd_in_pixel<R>(gyn, w, F, H, W, x + g, u);
         }
         float* out = gxn + (size_t)u * W + x;
         if (x + 8 <= W) {
