@@ -62,26 +62,88 @@ template <int R> struct BmLds {
     static constexpr int BYTES = 3 * TAB + 4 * WAVE;
 };
 
-// z at one pixel by FMAs
+typedef const float __attribute__((address_space(1))) gmem_t;
+typedef const float __attribute__((address_space(4))) taps_t;   // read by scalar loads
+typedef const v4f_any __attribute__((address_space(1))) gmem4_t;
+
+template <class P>
+__device__ __forceinline__ P* uniform(P* p) {
+    const unsigned long long a = (unsigned long long)p;
+    return reinterpret_cast<P*>((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32 |
+                                (unsigned)__builtin_amdgcn_readfirstlane((int)a));
+}
+
+// The pixels of rows u0 .. u1 that a wave has written as not finite, taken again by FMAs over the pixels of
+// gy in the image.
+// A lane has two pixels, which share the 2r + 2 values of a row of gy; the loads of three rows are in flight together, and
+// a wave whose sums are all NaN has nothing left to add.  A function of its own, called when the walk is over: within the
+// walk its registers spilled.  32 x 16 x 1024^2, r = 4, all pixels: one at a time within the walk 261 ms; so, NaN or
+// infinite gradients 1.1 ms (the FMA tiles 1.1) and finite sums past 2^80, which run to their end, 13 (1.3), waiting for
+// the nine rows that each output row reads again.
 template <int R>
-__device__ __attribute__((noinline)) float bwd_in_pixel(const float* __restrict__ gyn, const float* __restrict__ w, int F,
-                                                        int H, int W, int x, int y) {
-    constexpr int N = 2 * R + 1;
-    float acc = 0.f;
+__device__ __attribute__((noinline)) void bwd_in_again(const float* gyn_, const float* w_, float* gxn_, int F_, int H_, int W_,
+                                                       int x0_, int u0_, int u1_, float sc) {
+    constexpr int N = 2 * R + 1, NV = N + 1, GROUPS = (N + 2) / 3;
+    gmem_t* gyn = (gmem_t*)uniform(gyn_);
+    taps_t* w = (taps_t*)uniform(w_);
+    float* gxn = uniform(gxn_);
+    const int F = __builtin_amdgcn_readfirstlane(F_), H = __builtin_amdgcn_readfirstlane(H_),
+              W = __builtin_amdgcn_readfirstlane(W_), u0 = __builtin_amdgcn_readfirstlane(u0_),
+              u1 = __builtin_amdgcn_readfirstlane(u1_);
+    const int x = __builtin_amdgcn_readfirstlane(x0_) + 2 * ((int)threadIdx.x & 63);
+    const bool inside = __ballot(x < R || x + 2 + R > W) == 0;
+    unsigned cols = 0;   // bit i: column x - r + i lies in the image
+#pragma unroll
+    for (int i = 0; i < NV; ++i) cols |= (unsigned)(x - R + i >= 0 && x - R + i < W) << i;
 #pragma unroll 1
-    for (int f = 0; f < F; ++f)
+    for (int u = u0; u <= u1; ++u) {
+        float* o = gxn + (size_t)u * W + x;
+        const bool r0 = x < W && !(fabsf(o[0]) < __builtin_inff()), r1 = x + 1 < W && !(fabsf(o[1]) < __builtin_inff());
+        if (__ballot(r0 || r1) == 0) continue;
+        f2 acc = {0.f, 0.f};
 #pragma unroll 1
-        for (int j = 0; j < N; ++j) {
-            const int yy = y + R - j;
-            if (yy < 0 || yy >= H) continue;
-            const float* row = gyn + ((size_t)f * H + yy) * W;
-#pragma unroll 1
-            for (int i = 0; i < N; ++i) {
-                const int xx = x + R - i;
-                if (xx >= 0 && xx < W) acc = fmaf(w[((size_t)f * N + j) * N + i], row[xx], acc);
+        for (int e = 0; e < F * GROUPS; ++e) {
+            const int f = e / GROUPS, j0 = 3 * (e - f * GROUPS);
+            taps_t* wf = w + ((size_t)f * N + j0) * N;
+            float v[3][NV];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                gmem_t* row = gyn + ((size_t)f * H + clampi(u + R - j0 - j, H)) * W;
+                if (inside) {
+                    const v4f a = *(gmem4_t*)(row + x - R), b = *(gmem4_t*)(row + x - R + 4);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[j][i] = a[i], v[j][4 + i] = b[i];
+#pragma unroll
+                    for (int i = 8; i < NV; ++i) v[j][i] = row[x - R + i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) v[j][i] = row[clampi(x - R + i, W)];
+                }
             }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                if (j0 + j >= N || u + R - j0 - j < 0 || u + R - j0 - j >= H) continue;
+                if (inside) {
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        acc[0] = fmaf(wf[j * N + i], v[j][2 * R - i], acc[0]);
+                        acc[1] = fmaf(wf[j * N + i], v[j][2 * R - i + 1], acc[1]);
+                    }
+                } else {
+                    asm volatile("" : "+v"(cols));   // its bits are tested here, not kept as 2r + 2 lane masks
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        const float t = wf[j * N + i];
+                        if (cols >> (2 * R - i) & 1) acc[0] = fmaf(t, v[j][2 * R - i], acc[0]);
+                        if (cols >> (2 * R - i + 1) & 1) acc[1] = fmaf(t, v[j][2 * R - i + 1], acc[1]);
+                    }
+                }
+            }
+            if (__ballot((r0 && acc[0] == acc[0]) || (r1 && acc[1] == acc[1])) == 0) break;
         }
-    return acc;
+        if (r0) o[0] = sc * acc[0];
+        if (r1) o[1] = sc * acc[1];
+    }
 }
 
 template <int R>
@@ -216,6 +278,7 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
             __builtin_amdgcn_sched_barrier(0);
         });
     };
+    int bad0 = H, bad1 = -1;   // the first and the last row with a sum that may not be finite
     // output row u, complete in D's row b: the quarter of the wave that holds it writes 8 pixels per lane and clears it
     auto emit = [&](int u, int b, bool write) __attribute__((always_inline)) {
         float o[8];
@@ -231,16 +294,16 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
                 }
             }
         });
-        if (!write || !mine) return;
+        if (!write) return;
         const int x = x0 + 8 * m;
         float big = 0.f;   // a NaN or an infinity stays in the sum
 #pragma unroll
         for (int g = 0; g < 8; ++g) big += fabsf(o[g]), o[g] *= BM_DOWN;
-        if (!(big < __builtin_inff())) {
-#pragma unroll
-            for (int g = 0; g < 8; ++g)
-                if (x + g < W && !(fabsf(o[g]) < __builtin_inff())) o[g] = bwd_in_pixel<R>(gyn, w, F, H, W, x + g, u);
+        if (__ballot(mine && !(big < __builtin_inff()))) {
+            bad0 = min(bad0, u);
+            bad1 = u;
         }
+        if (!mine) return;
         float* out = gxn + (size_t)u * W + x;
         if (x + 8 <= W) {
             *reinterpret_cast<v4f_any*>(out) = sc * mk4(o[0], o[1], o[2], o[3]);
@@ -271,6 +334,10 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
         bp = b;
         b = b + 1 == N ? 0 : b + 1;
     }
+    if (bad1 < 0) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the other lanes' sums are read back
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    bwd_in_again<R>(gyn, w, gxn, F, H, W, x0, bad0, bad1, sc);
 }
 
 template <int R>
