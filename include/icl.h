@@ -30,8 +30,9 @@
  *  - Input and output images must not overlap (ICL_ERR_ALIAS): the paper's
  *    language forbids aliasing and local-memory staging needs read-only inputs
  *    (Section 5.2, memory spaces).
- *  - Arithmetic is float32 with float32 accumulation (unless the caller opts into
- *    ICL_MATH_F16_SPLIT, see icl_set_math); float16 / bfloat16 storage is decoded
+ *  - Arithmetic is float32 with float32 accumulation, or meets its error where float32
+ *    operands are carried in exact parts (ICL_MATH_F32, see icl_set_math), unless the
+ *    caller opts into ICL_MATH_F16_SPLIT; float16 / bfloat16 storage is decoded
  *    exactly on load and rounded to nearest even on store.
  *  - width == 0 or height == 0 is an empty image: the call returns ICL_OK and
  *    touches nothing.  Negative sizes are ICL_ERR_INVALID_VALUE.
@@ -415,9 +416,15 @@ icl_status icl_perf_model_fit_predict(const double* X, const double* y, int n, i
                                       double* yq, int hidden, int iters, unsigned long long seed);
 
 /* Arithmetic of the variants that tuning and default selection may pick.
- *   ICL_MATH_F32 (the default): only variants with float32 products and float32
- *     accumulation (vector FMA or the float32 matrix instructions), so every
- *     result meets the float32 error model of the conventions above.
+ *   ICL_MATH_F32 (the default): only variants with float32 accumulation of products that
+ *     are as good as float32's, so every result meets the float32 error model of the
+ *     conventions above:
+ *     "fp32_valu" and "fp32_mfma", float32 products (vector FMA, float32 matrix instructions);
+ *     "bf16x3_mfma" (icl_bank_bwd_input alone), each float32 operand the exact sum of three
+ *     bfloat16 parts and six of the nine products of parts, each exact: what is left out is
+ *     below 2^-26 |product|, a quarter of a float32 product's rounding.  Where its sums
+ *     leave float32's range scaled by 2^48 (from 2^80 on, infinities, NaN), float32 FMAs take their place.
+ *     A caller that wants float32 products there too forces "pers_p4x4_fold".
  *   ICL_MATH_F16_SPLIT: also the matrix-core 2-D correlation ("mfma_f16x3") that
  *     splits each float32 operand into float16 hi + lo parts and adds three
  *     float16 products with float32 accumulation.  Besides float32 rounding its
@@ -435,8 +442,7 @@ icl_math icl_get_math(void);
 /* Arithmetic a variant computes in (static string, NULL if out of range):
  *   "fp32_valu"   float32 vector FMA          "fp32_mfma"  float32 matrix instructions
  *   "fp16x3_mfma" float16 hi/lo split on the matrix cores (see ICL_MATH_F16_SPLIT)
- *   "bf16x3_mfma" float32 operands in three exact bfloat16 parts on the matrix cores, float32 accumulation; the
- *                 error is that of float32 sums or less (icl_bank_bwd_input)
+ *   "bf16x3_mfma" float32 operands in three exact bfloat16 parts on the matrix cores (see ICL_MATH_F32)
  *   "int32_valu"  exact integer arithmetic (icl_conv2d_u8): 32-bit, or bytes on the matrix cores with
  *                 32-bit accumulation ("mfma_i8") */
 const char* icl_variant_arith(icl_op op, int index);
