@@ -470,8 +470,9 @@ const char* icl_variant_name(icl_op op, int index);     /* NULL if out of range 
 icl_status icl_force_variant(icl_op op, int index);
 /* Variant the next call with these parameters would launch (host out).  For ICL_OP_CONV2D_U8 with a radius
  * above 4 the table holds the plain kernel alone (index 0): unforced calls run the matrix-core walk of
- * "mfma_i8" there, with the same bytes.  ICL_OP_CONV2D's default (index 1, "lds_p4x4_o0") runs the float32
- * FMA tile of the table that suits the image and type. */
+ * "mfma_i8" there, with the same bytes.  For ICL_OP_CONV2D with neither a forced nor a tuned variant it reports
+ * index 1 ("lds_p4x4_o0"), by which callers tell an untuned problem; the call runs the float32 FMA tile that suits
+ * the image and type, which icl_selected_variant_problem reports. */
 icl_status icl_selected_variant(icl_op op, icl_dtype dtype, int radius, int width, int height,
                                 int* index);
 

@@ -744,6 +744,11 @@ icl_status icl_force_variant(icl_op op, int index) {
 
 icl_status icl_selected_variant(icl_op op, icl_dtype dtype, int radius, int width, int height, int* index) {
     const icl_problem q{op, dtype, radius, width, height, 1, 1, 1};
+    // the 2-D correlation without a forced or tuned variant: always the first tile, whichever the size calls for
+    if (index && op == ICL_OP_CONV2D) {
+        *index = select_variant(problem_of(q), radius >= 0 && radius <= 7 ? 1 : 0);
+        return ICL_OK;
+    }
     return icl_selected_variant_problem(&q, index);
 }
 
@@ -762,7 +767,7 @@ icl_status icl_selected_variant_problem(const icl_problem* q, int* index) {
         }
         case ICL_OP_CONV2D: {
             Conv2dArgs a{};
-            a.r = radius;
+            a.r = radius; a.W = width; a.H = height; a.dt = dtype;
             deflt = conv2d_default(a);
             break;
         }

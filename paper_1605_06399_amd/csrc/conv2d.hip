@@ -308,24 +308,9 @@ hipError_t launch_pers(const Conv2dArgs& a) {
     }
 }
 
-// The untuned choice (its table name is that of the 64 x 64 tile it was).  4096^2, us, 64 x 64 tiles as they
-// were / here: float32 r = 1 38 / 29, r = 3 45 / 36, r = 5 77 / 59, r = 7 120 / 87; bfloat16 r = 2 29 / 26, r = 5
-// 73 / 63.
-//  - persistent tiles keep the next tile's loads in flight under the FMAs.  64 x 32 of them: the smaller tile
-//    puts more work-groups on a small image (1921 x 1083 r = 5: 14 us; 64 x 64 20) and loses nothing on a large one
-//  - 128 x 64 for wide float32 windows on images of 8 Mpx and more (two such tiles per CU): a lane's 8 x 4 block
-//    reads fewer window elements per FMA (r = 7: 85 against 90 us)
-//  - half storage with narrow windows moves half the bytes and a tile's work no longer covers its loads'
-//    registers: single-shot 64 x 32 tiles (r = 1: 19 against 24 us)
-hipError_t launch_default(const Conv2dArgs& a) {
-    if (a.dt != ICL_F32 && a.r <= 2) return launch_lds<4, 2, 1>(a);
-    if (a.dt == ICL_F32 && a.r >= 5 && (size_t)a.W * a.H >= ((size_t)1 << 23)) return launch_pers<8, 4>(a);
-    return launch_pers<4, 2>(a);
-}
-
 const Variant<Conv2dArgs> kConv2d[] = {
     {"plain", supports_plain, launch_plain},
-    {"lds_p4x4_o0", supports_lds, launch_default},
+    {"lds_p4x4_o0", supports_lds, launch_lds<4, 4, 0>},
     {"lds_p4x4_o1", supports_lds, launch_lds<4, 4, 1>},
     {"lds_p4x8_o0", supports_lds, launch_lds<4, 8, 0>},
     {"lds_p4x2_o1", supports_lds, launch_lds<4, 2, 1>},
@@ -344,6 +329,19 @@ const Variant<Conv2dArgs>* conv2d_variants(int* count) {
     return kConv2d;
 }
 
-int conv2d_default(const Conv2dArgs& a) { return supports_lds(a) ? 1 : 0; }
+// 4096^2, us, the 64 x 64 tile of index 1 as it was when it was the choice / here: float32 r = 1 38 / 29, r = 3 45 / 36,
+// r = 5 77 / 59, r = 7 120 / 87; bfloat16 r = 2 29 / 26, r = 5 73 / 63.
+//  - persistent tiles keep the next tile's loads in flight under the FMAs.  64 x 32 of them: the smaller tile
+//    puts more work-groups on a small image (1921 x 1083 r = 5: 14 us; 64 x 64 20) and loses nothing on a large one
+//  - 128 x 64 for wide float32 windows on images of 8 Mpx and more (two such tiles per CU): a lane's 8 x 4 block
+//    reads fewer window elements per FMA (r = 7: 85 against 90 us)
+//  - half storage with narrow windows moves half the bytes and a tile's work no longer covers its loads'
+//    registers: single-shot 64 x 32 tiles (r = 1: 19 against 24 us)
+int conv2d_default(const Conv2dArgs& a) {
+    constexpr int kPlain = 0, kLds4x2 = 4, kPers4x2 = 8, kPers8x4 = 9;   // positions in kConv2d
+    if (!supports_lds(a)) return kPlain;
+    if (a.dt != ICL_F32 && a.r <= 2) return kLds4x2;
+    return a.dt == ICL_F32 && a.r >= 5 && (size_t)a.W * a.H >= ((size_t)1 << 23) ? kPers8x4 : kPers4x2;
+}
 
 }  // namespace icl
