@@ -466,13 +466,17 @@ const char* icl_variant_name(icl_op op, int index);     /* NULL if out of range 
 /* Force a variant for every later call of `op` (-1 = back to tuned/default
  * selection); the analogue of the paper's directives that force optimisations
  * on or off.  A forced variant that cannot run a call (radius not compiled,
- * missing workspace) makes that call return ICL_ERR_UNSUPPORTED / ICL_ERR_WORKSPACE. */
+ * missing workspace) makes that call return ICL_ERR_UNSUPPORTED / ICL_ERR_WORKSPACE.
+ * Two variants accept more, forced, than their own kernel takes, and run another one
+ * there: "mfma_i8" (icl_conv2d_u8) the strips for radius 0 and rows under 16 pixels,
+ * "mfma_bf16x3_fold" (icl_bank_bwd_input) the float32 FMA tiles for radius 1 and 2, more
+ * than 16 filters and rows under 8 pixels.  Tuning and selection never take them there. */
 icl_status icl_force_variant(icl_op op, int index);
-/* Variant the next call with these parameters would launch (host out).  For ICL_OP_CONV2D_U8 with a radius
- * above 4 the table holds the plain kernel alone (index 0): unforced calls run the matrix-core walk of
- * "mfma_i8" there, with the same bytes.  For ICL_OP_CONV2D with neither a forced nor a tuned variant it reports
- * index 1 ("lds_p4x4_o0"), by which callers tell an untuned problem; the call runs the float32 FMA tile that suits
- * the image and type, which icl_selected_variant_problem reports. */
+/* Variant the next call with these parameters would launch (host out; rows without padding).  ICL_OP_CONV2D_U8
+ * reports "mfma_i8" above radius 4 too, where forcing it is unsupported, as forcing the strips is.  For
+ * ICL_OP_CONV2D with neither a forced nor a tuned variant it reports index 1 ("lds_p4x4_o0"), by which callers
+ * tell an untuned problem; the call runs the float32 FMA tile that suits the image and type, which
+ * icl_selected_variant_problem reports. */
 icl_status icl_selected_variant(icl_op op, icl_dtype dtype, int radius, int width, int height,
                                 int* index);
 

@@ -198,6 +198,13 @@ bool range_overlaps(const void* a, size_t an, const void* b, size_t bn) {
     return a0 < b0 + bn && b0 < a0 + an;
 }
 
+// The variant an unforced call runs: the tuned one where its own kernel takes these arguments, else the default.
+template <class A>
+int reported(const Problem& p, const Variant<A>* tab, const A& a, int deflt) {
+    const int v = select_variant(p, deflt);
+    return variant_forced(p.op) || tab[v].runs(a) ? v : deflt;
+}
+
 // Run the chosen variant; fall back to the default (or plain) when a tuned choice
 // cannot run these arguments.  Forced choices never fall back.
 template <class A>
@@ -207,10 +214,10 @@ icl_status dispatch(icl_op op, const Variant<A>* tab, int count, const A& a, int
         if (forced) return ICL_ERR_UNSUPPORTED;
         chosen = deflt;
     }
-    if (!tab[chosen].supports(a)) {
+    if (forced ? !tab[chosen].supports(a) : !tab[chosen].runs(a)) {
         if (forced) return ICL_ERR_UNSUPPORTED;
         chosen = deflt;
-        if (!tab[chosen].supports(a)) {
+        if (!tab[chosen].runs(a)) {
             chosen = 0;
             if (!tab[0].supports(a)) return ICL_ERR_UNSUPPORTED;
         }
@@ -404,11 +411,8 @@ icl_status icl_conv2d_u8(const uint8_t* src, size_t src_pitch, uint8_t* dst, siz
     int count;
     const Variant<U8Args>* tab = conv2d_u8_variants(&count);
     const int deflt = conv2d_u8_default(a);
-    const int v = select_variant(ICL_OP_CONV2D_U8, ICL_U8, radius, width, height, deflt, a.st);
-    // above the strips' radius the table holds the plain kernel alone: unforced calls take the matrix-core walk
-    if (v == 0 && deflt == 0 && !variant_forced(ICL_OP_CONV2D_U8) && supports_conv2d_u8_mfma(a))
-        return hip_status(launch_conv2d_u8_mfma(a));
-    return dispatch(ICL_OP_CONV2D_U8, tab, count, a, v, deflt);
+    return dispatch(ICL_OP_CONV2D_U8, tab, count, a,
+                    select_variant(ICL_OP_CONV2D_U8, ICL_U8, radius, width, height, deflt, a.st), deflt);
 }
 
 icl_status icl_harris(const float* src, size_t src_pitch, float* resp, size_t resp_pitch, int width, int height,
@@ -787,9 +791,10 @@ icl_status icl_selected_variant_problem(const icl_problem* q, int* index) {
         case ICL_OP_CONV_SEP_BATCHED: deflt = batched_default(); break;
         case ICL_OP_CONV2D_U8: {
             U8Args a{};
-            a.r = radius;
-            deflt = conv2d_u8_default(a);
-            break;
+            a.r = radius; a.W = width; a.H = height; a.sp = a.dp = (size_t)(width > 0 ? width : 0);
+            int count;
+            *index = reported(problem_of(*q), conv2d_u8_variants(&count), a, conv2d_u8_default(a));
+            return ICL_OK;
         }
         case ICL_OP_CONV3D_SEP: {
             Sep3Args a{};
@@ -808,8 +813,13 @@ icl_status icl_selected_variant_problem(const icl_problem* q, int* index) {
         case ICL_OP_BANK_FWD: case ICL_OP_BANK_BWD_INPUT: case ICL_OP_BANK_BWD_FILTER: {
             BankArgs a{};
             a.n = q->n; a.f = q->f; a.h = height; a.w = width; a.r = radius;
+            if (op == ICL_OP_BANK_BWD_INPUT) {
+                int count;
+                *index = reported(problem_of(*q), bank_bwd_input_variants(&count), a, bank_bwd_input_default(a));
+                return ICL_OK;
+            }
             deflt = op == ICL_OP_BANK_FWD ? bank_fwd_default(a)
-                    : op == ICL_OP_BANK_BWD_INPUT ? bank_bwd_input_default(a) : bank_bwd_filter_default(a);
+                                        : bank_bwd_filter_default(a);
             break;
         }
         case ICL_OP_BANK_FWD_SSE: {

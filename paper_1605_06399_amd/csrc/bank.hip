@@ -1318,7 +1318,7 @@ bool supports_bwd_w(const BankArgs& a) {
 bool supports_bwd_wm(const BankArgs& a) { return supports_bwd_w(a) && a.f <= 16; }
 
 
-// on the matrix cores for radius 3 and 4 and up to 16 filters, else the FMA tiles
+// on the matrix cores for radius 3 and 4 and up to 16 filters, else (forced only) the FMA tiles
 template <int R> hipError_t edge_R(const BankArgs& a) { return launch_edge<R>(a); }
 hipError_t launch_edges(const BankArgs& a) { ICL_BANK_SWITCH(edge_R) }
 hipError_t launch_bwd_in_mfma(const BankArgs& a) {
@@ -1330,7 +1330,7 @@ hipError_t launch_bwd_in_mfma(const BankArgs& a) {
 const Variant<BankArgs> kBwdIn[] = {{"plain", supports_bank, launch_bwd_in_plain},
                                     {"tile64_p4x4_fold", supports_bank, launch_bwd_in},
                                     {"pers_p4x4_fold", supports_pers, launch_bwd_in_pers},
-                                    {"mfma_bf16x3_fold", supports_bank, launch_bwd_in_mfma}};
+                                    {"mfma_bf16x3_fold", supports_bank, launch_bwd_in_mfma, supports_bank_bwd_in_mfma}};
 const Variant<BankArgs> kBwdW[] = {{"wave_t32x64", supports_bwd_w, launch_bwd_w},
                                    {"block4_t64", supports_bwd_w, launch_bwd_w4},
                                    {"block4_t64x256", supports_bwd_w, launch_bwd_w4x4},

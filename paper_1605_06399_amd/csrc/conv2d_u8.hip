@@ -285,8 +285,8 @@ hipError_t launch_strip(const U8Args& a) {
 
 bool supports_strip(const U8Args& a) { return a.r >= 0 && a.r <= U8_STRIP_MAX_R; }
 
-// The matrix-core walk as a table entry: radius 1 .. 4 (the range of the strips; a radius of 0 and rows
-// under 16 pixels run the strips).
+// The matrix-core walk as a table entry: selected for radius 1 .. 7 and rows of 16 pixels on; forced it takes the
+// strips' range, radius 0 .. 4, and runs the strips for a radius of 0 and shorter rows.
 hipError_t launch_mfma(const U8Args& a) {
     return a.r >= 1 && supports_conv2d_u8_mfma(a) ? launch_conv2d_u8_mfma(a) : launch_strip<16, 4>(a);
 }
@@ -300,7 +300,7 @@ const Variant<U8Args> kConv2dU8[] = {
     {"strip_p4_t24", supports_strip, launch_strip<24, 4>},
     {"strip_p4_t16_q16", supports_strip, launch_strip<16, 4, 16>},
     {"strip_p4_t12_q16", supports_strip, launch_strip<12, 4, 16>},
-    {"mfma_i8", supports_strip, launch_mfma},
+    {"mfma_i8", supports_strip, launch_mfma, supports_conv2d_u8_mfma},
 };
 
 }  // namespace
@@ -310,8 +310,7 @@ const Variant<U8Args>* conv2d_u8_variants(int* count) {
     return kConv2dU8;
 }
 
-// mfma_i8 for radius 1 .. 4, the strips for 0; wider windows are plain in the table, and the entry point runs
-// the matrix-core walk for them
-int conv2d_u8_default(const U8Args& a) { return !supports_strip(a) ? 0 : a.r >= 1 ? 8 : 1; }
+// mfma_i8 wherever it runs, else the strips, else plain
+int conv2d_u8_default(const U8Args& a) { return supports_conv2d_u8_mfma(a) ? 8 : supports_strip(a) ? 1 : 0; }
 
 }  // namespace icl

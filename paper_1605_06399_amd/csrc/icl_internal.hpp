@@ -100,8 +100,12 @@ struct BankSseArgs {
 // One precompiled candidate implementation of an operation.
 template <class A> struct Variant {
     const char* name;
-    bool (*supports)(const A&);        // can this variant run these arguments?
+    bool (*supports)(const A&);        // can this variant, forced, run these arguments?
     hipError_t (*launch)(const A&);
+    // Where the kernel of this name runs, if that is not where the variant is supported: a forced variant may go through
+    // another kernel outside its own range, tuning and selection take it in that range only.
+    bool (*own)(const A&) = nullptr;
+    bool runs(const A& a) const { return own ? own(a) : supports(a); }
 };
 
 // Small neural-network time model of the model-guided tuner (host code).

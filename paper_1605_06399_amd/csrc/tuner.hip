@@ -311,7 +311,7 @@ icl_status search(const Problem& pb, const Variant<A>* tab, int count, int sets,
     // every variant but the reference (index 0) that runs the problem under the arithmetic mode
     std::vector<int> cand;
     for (int i = 1; i < count; ++i)
-        if (variant_allowed(op, i) && tab[i].supports(make(0, i))) cand.push_back(i);
+        if (variant_allowed(op, i) && tab[i].supports(make(0, i)) && tab[i].runs(make(0, i))) cand.push_back(i);
     g_plan.timed = 0;
     const int ns = std::max(2, g_plan.samples);
     if (!g_plan.model || (int)cand.size() <= ns + std::max(1, g_plan.top_k)) {
