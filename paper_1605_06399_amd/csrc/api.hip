@@ -139,7 +139,16 @@ icl_status device_ready() {
 
 static std::mutex g_occ_mu;
 static std::vector<std::pair<const void*, int>> g_occ;   // kernel -> resident blocks on the device
-static int g_cus = 0;
+
+int device_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+        return ok && n > 0 ? n : 1;
+    }();
+    return cus;
+}
 
 int persistent_grid(const void* kernel, int block, int ntiles) {
     int resident = 0;
@@ -148,16 +157,10 @@ int persistent_grid(const void* kernel, int block, int ntiles) {
         for (const auto& e : g_occ)
             if (e.first == kernel) resident = e.second;
         if (resident == 0) {
-            if (g_cus == 0) {
-                int dev = 0;
-                if (hipGetDevice(&dev) != hipSuccess ||
-                    hipDeviceGetAttribute(&g_cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-                    g_cus = 1;
-            }
             int per_cu = 0;
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, 0) != hipSuccess || per_cu < 1)
                 per_cu = 1;
-            resident = per_cu * g_cus;
+            resident = per_cu * device_cus();
             g_occ.push_back({kernel, resident});
         }
     }

@@ -344,13 +344,14 @@ template <int R>
 hipError_t launch_R(const BankArgs& a) {
     const int strips = (a.w + BM_COLS - 1) / BM_COLS;
     const long long per = (long long)a.n * strips;
-    // rows per wave: the split into row blocks whose rounds of 2048 resident waves walk the fewest rows
+    // rows per wave: the split into row blocks whose rounds of resident waves (two per SIMD) walk the fewest rows
+    const long long resident = 8 * device_cus();
     const int most = (a.h + 15) / 16;
     int nblk = 1;
     long long best = -1;
     for (int k = 1; k <= most && k <= 256; ++k) {
         const int th = (a.h + k - 1) / k;
-        const long long rounds = (per * k + 2047) / 2048, cost = rounds * (th + 2 * R);
+        const long long rounds = (per * k + resident - 1) / resident, cost = rounds * (th + 2 * R);
         if (best < 0 || cost < best) best = cost, nblk = k;
         if (rounds > 16) break;
     }

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256, waves_per_simd(R)) void conv2d_u8_mfma_k(const
 template <int R>
 hipError_t launch_R(const U8Args& a) {
     const int nstrips = (a.W + UW - 1) / UW;
-    const int slots = 1024 * waves_per_simd(R);   // waves resident on 256 CUs
+    const int slots = 4 * device_cus() * waves_per_simd(R);   // resident waves
     const int want = slots / nstrips > 1 ? slots / nstrips : 1;
     int th = (a.H + want - 1) / want;
     if (th < 8) th = 8;

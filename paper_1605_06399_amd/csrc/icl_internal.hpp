@@ -205,6 +205,8 @@ const char* op_name(icl_op op);
 // Grid for a persistent tile loop: resident blocks of `kernel` on the whole device
 // (occupancy x CUs, cached per kernel), at most `ntiles`, rounded down to a multiple of 8.
 int persistent_grid(const void* kernel, int block, int ntiles);
+// Compute units of the device (queried once; 1 if that fails).
+int device_cus();
 
 // Zero-fill `n` floats with a kernel (no memset node, so it is safe inside captured graphs).
 hipError_t zero_fill(float* p, size_t n, hipStream_t st);
