@@ -33,6 +33,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 FP32_FMA_PEAK_TFLOPS = 78.6    # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz, packed FP32 disabled
 FP32_PACKED_PEAK_TFLOPS = 157.3
 FP16_MFMA_PEAK_TFLOPS = 2500.0  # dense FP16 matrix cores, published
+BF16X3_PEAK_TFLOPS = 2500.0 / 6.0   # float32 operands in bfloat16 parts: six dense bfloat16 products each
 EXTRAS = ("corner", "batch", "bank", "paper", "tuner", "volume")
 INT_DOT2_PEAK_TMACS = 78.6     # v_dot2_i32_i16: 2 int16 MACs per lane per issue, 256 CU x 64 lanes x 2.4 GHz
 METRIC = "Gpixel/s & % HBM peak, autotuned vs plain kernel; fwd+bwd Gpixel/s"
@@ -80,6 +81,12 @@ def roof_gpx(kind, r, bytes_px=8.0):
 # kernel source files per call kind: traffic figures are valid only for the source they were taken on
 KERNEL_SOURCES = {"2d": ["conv2d.hip", "conv2d_mfma.hip", "tile_stage.hpp", "corr_tile.hpp", "icl_device.hpp"],
                   "sep": ["conv_sep.hip", "sep_tile.hpp", "sep_strip.hpp", "tile_stage.hpp", "icl_device.hpp"]}
+
+
+def unit_peak_tflops(arith):
+    """Peak of the unit that a float32 variant's arithmetic runs on, in useful float32 operations."""
+    return {"fp32_mfma": FP32_PACKED_PEAK_TFLOPS, "bf16x3_mfma": BF16X3_PEAK_TFLOPS,
+            "fp32_valu": FP32_FMA_PEAK_TFLOPS}[arith]
 
 
 def source_hash(*names):
@@ -212,24 +219,26 @@ WORKLOAD_KERNELS = [
     ("batch", r"sep_batched_col_k<icl::(F16|BF16), (\d), (\d+)>", "colwalk_cx{1}_step{2}_{0}",
      ["batched.hip", "sep_colwalk.hpp", "sep_tile.hpp", "tile_stage.hpp", "icl_device.hpp"], 4 * _B_PX),
     ("corner", r"harris_(fused|strips)<(\d+), (\d+)(?:, (?:true|false))?>", "harris_{0}_t{2}", ["harris.hip", "harris_strip.hpp",
-     "icl_device.hpp"], 8 * 8192 * 8192),
+     "tile_stage.hpp", "icl_device.hpp"], 8 * 8192 * 8192),
     ("corner", r"nms_stream<(\d+)>", "nms_stream_t{0}", ["nms.hip", "harris_strip.hpp", "icl_device.hpp"],
      5 * 8192 * 8192),
     ("corner", r"nms_stream_a<(\d+), (true|false)>", "nms_stream_a_t{0}_sm:{1}", ["nms.hip", "harris_strip.hpp",
      "icl_device.hpp"], 5 * 8192 * 8192),
     ("corner", r"corners_stream<(\d+), (\d+)>", "corners_stream_t{1}", ["corners.hip", "harris_strip.hpp",
-     "icl_device.hpp"], 5 * 8192 * 8192),
+     "tile_stage.hpp", "icl_device.hpp"], 5 * 8192 * 8192),
     ("bank", r"bank_fwd_(mfma_k<4, true, \d+, (?:true|false)>|pers_k<4, true>|sse_tpre_k<4>)", "fwd_sse:{0}",
      ["bank.hip"],
      4 * (_BANK[0] * _BANK[2] + 2 * _BANK[0] * _BANK[1] * _BANK[2])),
-    ("bank", r"bank_bwd_in_(mfma_k|pers_k|k)<4>", "bwd_input:{0}", ["bank.hip", "bank_bwd_in_mfma.hip"],
+    ("bank", r"bank_bwd_in_(mfma_k|pers_k|k)<4>", "bwd_input:{0}", ["bank.hip", "bank_bwd_in_mfma.hip", "tile_stage.hpp",
+                                                                      "icl_device.hpp"],
      4 * (_BANK[0] * _BANK[1] * _BANK[2] + _BANK[0] * _BANK[2])),
-    ("bank", r"bank_bwd_(wm_k<4, \d, (?:true|false)(?:, (?:true|false))?>|w4_k<4, \d, 16>)", "bwd_filter:{0}",
-     ["bank.hip"],
+    ("bank", r"bank_bwd_(wm_k<4, \d, (?:true|false)(?:, (?:true|false))?>|w4_k<4, \d, 16>|ws_k<4>)", "bwd_filter:{0}",
+     ["bank.hip", "tile_stage.hpp", "icl_device.hpp"],
      4 * (_BANK[0] * _BANK[1] * _BANK[2] + _BANK[0] * _BANK[2])),
     ("paper", r"sep_(fused|pers)<icl::F32, 2, (\d+), (\d+)>", "sep5_constant:{0}_t{1}_c{2}",
      KERNEL_SOURCES["sep"], 8 * 4096 * 4096),
-    ("paper", r"conv2d_u8_mfma_k<2>", "u8_5x5:mfma_i8", ["conv2d_u8_mfma.hip", "icl_device.hpp"], 2 * 8192 * 8192),
+    ("paper", r"conv2d_u8_mfma_k<2>", "u8_5x5:mfma_i8", ["conv2d_u8_mfma.hip", "u8_rows.hpp", "icl_device.hpp"],
+     2 * 8192 * 8192),
     ("paper", r"u8_strip<2, (\d+), (\d+), (\d+)>", "u8_5x5:strip_p{1}_t{0}_q{2}", ["conv2d_u8.hip", "icl_device.hpp"],
      2 * 8192 * 8192),
     ("volume", r"sep3_stream<icl::F32, (\d+), (\d+)>", "sep3d_r{0}:stream_z{1}", ["conv3d.hip", "icl_device.hpp"],
@@ -416,7 +425,7 @@ SQ_RUNS = {"sweep": "--steps 3 --warmup 1 --no-extras --no-cpu", "bank": "--only
            "batch": "--only batch --steps 4 --warmup 1 --no-cpu", "corner": "--only corner --steps 4 --warmup 1 --no-cpu",
            "paper": "--only paper --steps 4 --warmup 1 --no-cpu"}
 SQ_KERNELS = (r"conv2d_pers<F32, [1-7], ", r"sep_(fused|pers)<F32, [1-7], ", r"bank_(fwd_mfma_k<4, true, 0, true>|"
-              r"bwd_in_(?:pers|mfma)_k<4>|bwd_wm_k<4, 4, true, (?:true|false)>)", r"sep_batched_col_k<F16, 1, 64>", r"harris_strips<2, 16, false>",
+              r"bwd_in_(?:pers|mfma)_k<4>|bwd_wm_k<4, 4, true, (?:true|false)>|bwd_ws_k<4>|bwd_edge_k<4>)", r"sep_batched_col_k<F16, 1, 64>", r"harris_strips<2, 16, false>",
               r"nms_stream_a<4, false>", r"corners_stream<2, 32>", r"conv2d_u8_mfma_k<2>", r"u8_strip<2, \d+, \d+, \d+>")
 
 
@@ -1145,13 +1154,12 @@ def extra_bank(torch, B, T, synth, steps):
         finally:
             B.icl_force_variant(B.ICL_OP_BANK_BWD_FILTER, -1)
         per_variant_w[B.icl_variant_name(B.ICL_OP_BANK_BWD_FILTER, v)] = round(fv * 1e3, 3)
-    # each phase against the peak of the unit its kernel runs on: float32 matrix instructions
-    # (157.3 TFLOP/s) or float32 vector FMA (78.6, packed FMA disabled)
+    # each phase against the peak of the unit its kernel runs on
     flops_phase = 2 * 81 * N * F * Hb * Wb
     phases_out, roof_time = {}, 0.0
     for k in ("fwd_loss", "bwd_input", "bwd_filter"):
         ar = B.icl_variant_arith(ops[k], sel[k])
-        peak = FP32_PACKED_PEAK_TFLOPS if ar == "fp32_mfma" else FP32_FMA_PEAK_TFLOPS
+        peak = unit_peak_tflops(ar)
         tf = flops_phase / (ph[k] * 1e-3) / 1e12
         roof_time += flops_phase / (peak * 1e12)
         phases_out[k] = {"ms": ph[k], "variant": B.icl_variant_name(ops[k], sel[k]), "arith": ar,
