@@ -1064,7 +1064,7 @@ hipError_t bwd_wm_RT(const BankArgs& a) {
 // The same product for problems of few tiles: tiles of 64 columns x 16 rows (four rows per wave) walked by a
 // grid of `parts` work-groups, one partial each.  A 64 x 256 tile per work-group leaves most of the chip idle
 // up to some hundreds of tiles, and its four staged sub-tiles run one after another: 4 x 8 x 201 x 200, r = 2
-// is 16 of them and took 95 us; here 208 tiles on 112 work-groups take 22 (16 x 16 x 512^2, r = 4, 256 of
+// is 16 of them and took 92 us; here 208 tiles on 112 work-groups take 20 (16 x 16 x 512^2, r = 4, 256 of
 // them: 160 and 125 us).  The number of work-groups is bounded by the partials that the workspace is sized for.  Taps on the matrix cores and, where one is alone in its 16-tap block, the tail
 // as above; the steps take pixel-strided pixels (16 q + st).
 constexpr int GWS_H = 16;

@@ -15,7 +15,7 @@
 // consecutive pixels.  Rows of gy are loaded a row ahead, a lane having 4 pixels of 8 filters, and written to LDS as
 // records of one pixel's 8 filters; each wave has its own, so there is no barrier.
 //
-// Bound by the matrix cores: 32 x 16 x 1024^2, r = 4, takes 1.09e15 operations of them (9 of 16 rows of D and 9 of 10
+// Bound by the matrix cores: 32 x 16 x 1024^2, r = 4, takes 1.09e12 operations of them (9 of 16 rows of D and 9 of 10
 // taps of the pairs are of use, six products per pair of operands) in 0.86 ms = 1.27 PFLOP/s, with 2.3 GB of gy read
 // meanwhile; the FMA tiles took 1.11 ms.  Two waves per SIMD (one alone issues these products at half rate); the operands
 // of the next products are loaded under these (0.84 against 0.86 without).  The split of the next row between the
