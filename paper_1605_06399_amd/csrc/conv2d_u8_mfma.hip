@@ -16,9 +16,9 @@
 // branch for the whole wave).  The sums start at 128 sum(w) (the pixels are taken off by 128) and the rounding bias;
 // int32 wraps, and the result fits (r <= 7), so it is exact whatever wraps on the way.
 //
-// Bound: memory up to r = 3 (48 us at 8192^2, r = 2, of which a copy of the bytes takes 27), the products
+// Bound: memory up to r = 3 (46 us at 8192^2, r = 2, of which a copy of the bytes takes 27), the products
 // beyond (2 (r + 1) of 16 cycles per 256 pixels).  The dot-product strips issue 24 vector instructions per
-// pixel there.  Per call at 8192^2, strips / here: r = 1 44 / 44 us, 2 56 / 48, 3 85 / 50, 4 122 / 68;
+// pixel there.  Per call at 8192^2, strips / here: r = 1 44 / 44 us, 2 56 / 46, 3 85 / 50, 4 122 / 68;
 // plain / here: r = 5 3370 / 72, r = 7 5940 / 90.  At 512^2 both sit at the call's own 10 us.
 // Strips at the image's left and right edge first cost twice a step of the others and set the kernel's end
 // (52 us): they read past the row's ends and mask, and only the image's first and last rows shift bytes.
@@ -75,7 +75,7 @@ __device__ __forceinline__ void u8_walk(const uint8_t* __restrict__ src, size_t 
     const unsigned rowoff = half ? (unsigned)sp : 0u;
     // Rows whose columns left of 0 or right of W - 1 could lie outside the image's memory (its first row and its last
     // ones): an edge strip reads those from clamped columns, all others straight, into the padding or neighbour rows.
-    auto guarded = [&](int k) { return !u8_straight(y0 - R + k, H, tail); };
+    auto guarded = [&](int k) { return u8_guarded(y0 - R + k, tail); };
     auto load_row = [&](int k) -> v4i {   // row pair y0 - R + k, read clamped: this lane's row of it
         const int q = y0 - R + k;
         const uint8_t* row = src + (size_t)u8_row(q, H) * sp;
@@ -136,20 +136,25 @@ __device__ __forceinline__ void u8_walk(const uint8_t* __restrict__ src, size_t 
             const int k = kb + s;
             v4i x = ring[s];
             ring[s] = load_row(k + UQ);
-            if constexpr (!INSIDE) {
+            const int q = y0 - R + k;
+            auto outside = [&]() {   // rows outside the image
+                if (cmode && (q < 0 || q + 1 >= H)) {
+                    const bool out = q + half < 0 || q + half >= H;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[i] = out ? (int)cfill : x[i];
+                }
+            };
+            if constexpr (INSIDE) {
+                outside();
+            } else {
                 const uint32_t fill = cmode ? cfill : ends[s] * 0x01010101u;
                 ends[s] = load_end(k + UQ);
-                if (guarded(k)) {
+                if (guarded(k)) {   // they are guarded
                     x = bytes_fix(x, c, cb, fill);
+                    outside();
                 } else {
                     x = (x & keep) | (v4i{(int)fill, (int)fill, (int)fill, (int)fill} & ~keep);
                 }
-            }
-            const int q = y0 - R + k;
-            if (cmode && (q < 0 || q + 1 >= H)) {
-                const bool out = q + half < 0 || q + half >= H;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = out ? (int)cfill : x[i];
             }
             x ^= (int)0x80808080;
 #pragma unroll
@@ -240,7 +245,7 @@ hipError_t launch_R(const U8Args& a) {
     const int words = (uintptr_t)a.dst % 4 == 0 && a.dp % 4 == 0;
     hipLaunchKernelGGL(conv2d_u8_mfma_k<R>, dim3(grid_pad8((items + 3) / 4)), dim3(256), 0, a.st, a.src, a.sp, a.dst,
                        a.dp, a.W, a.H, a.taps, a.shift, nstrips, (int)items, th, words,
-                       u8_tail_rows(a.W, (unsigned)a.sp), a.cmode, a.cval);
+                       u8_tail(a.W, a.H, (unsigned)a.sp), a.cmode, a.cval);
     return hipGetLastError();
 }
 

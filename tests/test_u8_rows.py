@@ -1,7 +1,7 @@
 """The addresses of the unsigned char walk, enumerated on the host: every 16-byte read of every strip, row and lane,
 taken from the header that the kernel computes them with, lies in the image's memory (H - 1 rows of the pitch and the W
 bytes of the last), for widths around a strip's 256 columns, few and many rows and padded rows; rows as wide as a
-strip's reads are clamped in the first and the last two only."""
+strip's reads are clamped in the first and the last two only, and rows outside the image are clamped ones."""
 import os
 import shutil
 import subprocess
@@ -25,7 +25,7 @@ int main() {
             for (int pad : pads) {
                 const unsigned sp = W + pad;
                 const long long size = (long long)(H - 1) * sp + W;
-                const int tail = u8_tail_rows(W, sp);
+                const int tail = u8_tail(W, H, sp);
                 for (int xs = 0; xs < W; xs += U8_COLS) {
                     for (int q = -7; q < H + 30; ++q)
                         for (int lane = 0; lane < 64; ++lane) {
@@ -33,8 +33,9 @@ int main() {
                             const int cb = std::min(std::max(c, 0), W - 16);
                             const long long at = (long long)u8_row(q, H) * sp + u8_lane(q, H, tail, g >> 1 ? sp : 0u, c, cb);
                             ++reads;
-                            const bool wide_guarded = W >= U8_RIGHT && q >= 1 && q + 1 < H - 1 && !u8_straight(q, H, tail);
-                            if (at < 0 || at + 16 > size || (u8_inside(xs, W) && c != cb) || wide_guarded) {
+                            const bool wide_guarded = W >= U8_RIGHT && q >= 1 && q + 1 < H - 1 && u8_guarded(q, tail);
+                            const bool outside_free = (q < 0 || q + 1 >= H) && !u8_guarded(q, tail);
+                            if (at < 0 || at + 16 > size || (u8_inside(xs, W) && c != cb) || wide_guarded || outside_free) {
                                 std::printf("W=%d H=%d pitch=%u strip %d row %d lane %d: bytes %lld..%lld of %lld\n", W, H, sp,
                                             xs, q, lane, at, at + 15, size);
                                 return 1;
