@@ -1163,7 +1163,7 @@ def extra_bank(torch, B, T, synth, steps):
         tf = flops_phase / (ph[k] * 1e-3) / 1e12
         roof_time += flops_phase / (peak * 1e12)
         phases_out[k] = {"ms": ph[k], "variant": B.icl_variant_name(ops[k], sel[k]), "arith": ar,
-                         "tflops": round(tf, 2), "peak_tflops": peak, "frac": round(tf / peak, 3)}
+                         "tflops": round(tf, 2), "peak_tflops": round(peak, 1), "frac": round(tf / peak, 3)}
     flops = 3 * flops_phase
     res["filter_bank_fwd_bwd"] = {"ms": round(dt * 1e3, 3), "gpx_s": round(N * Hb * Wb / dt / 1e9, 2),
                                   "output_gpx_s": round(N * F * Hb * Wb / dt / 1e9, 1),
