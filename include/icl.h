@@ -467,8 +467,9 @@ const char* icl_variant_name(icl_op op, int index);     /* NULL if out of range 
  * selection); the analogue of the paper's directives that force optimisations
  * on or off.  A forced variant that cannot run a call (radius not compiled,
  * missing workspace) makes that call return ICL_ERR_UNSUPPORTED / ICL_ERR_WORKSPACE.
- * Two variants accept more, forced, than their own kernel takes, and run another one
- * there: "mfma_i8" (icl_conv2d_u8) the strips for radius 0 and rows under 16 pixels,
+ * Three variants accept more, forced, than their own kernel takes, and run another one
+ * there: "strips_any_t8" (icl_nms) the row kernel for images of under 256 columns and the
+ * plain one for radius 2 and more, "mfma_i8" (icl_conv2d_u8) the strips for radius 0 and rows under 16 pixels,
  * "mfma_bf16x3_fold" (icl_bank_bwd_input) the float32 FMA tiles for radius 1 and 2, more
  * than 16 filters and rows under 8 pixels.  Tuning and selection never take them there. */
 icl_status icl_force_variant(icl_op op, int index);

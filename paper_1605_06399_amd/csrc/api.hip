@@ -787,9 +787,10 @@ icl_status icl_selected_variant_problem(const icl_problem* q, int* index) {
         }
         case ICL_OP_NMS: {
             NmsArgs a{};
-            a.r = radius;
-            deflt = nms_default(a);
-            break;
+            a.r = radius; a.W = width; a.H = height;
+            int count;
+            *index = reported(problem_of(*q), nms_variants(&count), a, nms_default(a));
+            return ICL_OK;
         }
         case ICL_OP_CONV_SEP_BATCHED: deflt = batched_default(); break;
         case ICL_OP_CONV2D_U8: {

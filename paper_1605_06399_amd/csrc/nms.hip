@@ -22,8 +22,9 @@
 //                all 64 lanes own outputs, 1 KiB row reads and 256-byte mask writes, the two
 //                outside columns as broadcast values; the last strip of another width ends at
 //                the last column.  _sm: strip-major wave order.
-//   strips_any_t8: the stream_a strips of 8 rows for rows of any alignment, row4 below 256
-//                columns, plain for wider windows (the default for r = 1).
+//   strips_any_t8: the stream_a strips of 8 rows for rows of any alignment (the default for
+//                r = 1 from 256 columns on; forced it runs row4 on narrower images and plain
+//                for wider windows).
 #include "harris_strip.hpp"
 #include "icl_device.hpp"
 #include "icl_internal.hpp"
@@ -306,12 +307,13 @@ hipError_t launch_stream_a(const NmsArgs& a) {
 }
 
 // The default: strips of 8 rows from 256 columns on, rows of any alignment (their vector accesses need none; the
-// strip entries of the table refuse rows off 16 bytes), row4 for narrower images, the plain kernel for wider windows.
+// other strip entries of the table refuse rows off 16 bytes).
 // 8192^2: 115 us in strips of 64 rows, 63 in strips of 8 (more waves, each row still read about once);
 // 1919 x 1081, rows off 16 bytes: row4 11 us, strips 5.
-hipError_t launch_any(const NmsArgs& a) {
+bool runs_any(const NmsArgs& a) { return a.r == 1 && a.W >= 256; }
+hipError_t launch_any(const NmsArgs& a) {   // forced, every image
     if (a.r != 1) return launch_plain(a);
-    return a.W >= 256 ? launch_stream_a<8, false>(a) : launch_row4(a);
+    return runs_any(a) ? launch_stream_a<8, false>(a) : launch_row4(a);
 }
 
 const Variant<NmsArgs> kNms[] = {
@@ -326,7 +328,7 @@ const Variant<NmsArgs> kNms[] = {
     {"stream_a_t4", supports_stream_a, launch_stream_a<4, false>},
     {"stream_a_t32_sm", supports_stream_a, launch_stream_a<32, true>},
     {"stream_a_t16_sm", supports_stream_a, launch_stream_a<16, true>},
-    {"strips_any_t8", supports_plain, launch_any},
+    {"strips_any_t8", supports_plain, launch_any, runs_any},
 };
 
 }  // namespace
@@ -336,6 +338,7 @@ const Variant<NmsArgs>* nms_variants(int* count) {
     return kNms;
 }
 
-int nms_default(const NmsArgs& a) { return a.r == 1 ? 11 : 0; }   // strips_any_t8
+// strips_any_t8 where its strips run, row4 for narrower images, plain for wider windows
+int nms_default(const NmsArgs& a) { return a.r != 1 ? 0 : runs_any(a) ? 11 : 1; }
 
 }  // namespace icl

@@ -29,6 +29,11 @@ def test_unsigned_char_correlation(r, w, name):
     assert B.icl_variant_name(B.ICL_OP_CONV2D_U8, v) == name
 
 
+@pytest.mark.parametrize("r,w,name", [(1, 256, "strips_any_t8"), (1, 255, "row4"), (1, 1, "row4"), (2, 512, "plain")])
+def test_nms(r, w, name):
+    assert selected(B.ICL_OP_NMS, B.ICL_F32, r, w, 512) == name
+
+
 @pytest.mark.parametrize("op,dtype,r,w,h,kw,entry,name", [
     # the tuned entry's own kernel takes the call: it runs
     (B.ICL_OP_CONV2D_U8, B.ICL_U8, 5, 512, 512, {}, "plain", "plain"),
