@@ -16,7 +16,7 @@
 // records of one pixel's 8 filters; each wave has its own, so there is no barrier.
 //
 // Bound by the matrix cores: 32 x 16 x 1024^2, r = 4, takes 1.09e12 operations of them (9 of 16 rows of D and 9 of 10
-// taps of the pairs are of use, six products per pair of operands) in 0.86 ms = 1.27 PFLOP/s, with 2.3 GB of gy read
+// taps of the pairs are of use, six products per pair of operands) in 0.83 ms = 1.31 PFLOP/s, with 2.3 GB of gy read
 // meanwhile; the FMA tiles took 1.11 ms.  Two waves per SIMD (one alone issues these products at half rate); the operands
 // of the next products are loaded under these (0.84 against 0.86 without).  The split of the next row between the
 // products instead of between the rows spilled and was slower (0.90).
@@ -27,7 +27,8 @@
 // gy and w are split after a scaling by 2^24, which is exact, and the sums scaled back: the last bit of the smallest
 // float32 (2^-149) is then a normal bfloat16, so that no operand below 2^104 loses bits in its split (unscaled, one below
 // 2^-110 did: gy 1e-37 under taps of 1e12 erred by 3e-4 of the result, float32 FMAs by 7e-7).  The scaling costs a
-// multiplication per staged value and no time that can be measured.
+// multiplication per staged value (1.5 % of the kernel); scaling back within the caller's factor and no test for small
+// sums give more than that back (with the border 898 us unscaled, 880 so).
 // Infinite, NaN or overflowing values turn every sum that meets them in a zero of A, or in the split, into a NaN, and
 // scaled sums from 2^80 on are infinite: sums that are not finite are taken again by FMAs.
 #include "icl_device.hpp"
@@ -71,6 +72,19 @@ __device__ __forceinline__ P* uniform(P* p) {
     const unsigned long long a = (unsigned long long)p;
     return reinterpret_cast<P*>((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32 |
                                 (unsigned)__builtin_amdgcn_readfirstlane((int)a));
+}
+
+// A wave's lanes read back what others of them have written.
+__device__ __forceinline__ void own_writes() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Rows u0 .. u1 - 1 of a wave's columns times the caller's factor.
+__device__ __attribute__((noinline)) void bwd_in_times(float* gxn, int W, int x0, int u0, int u1, float factor) {
+#pragma unroll 1
+    for (int u = u0; u < u1; ++u)
+        for (int x = x0 + ((int)threadIdx.x & 63); x < min(x0 + BM_COLS, W); x += 64) gxn[(size_t)u * W + x] *= factor;
 }
 
 // The pixels of rows u0 .. u1 that a wave has written as not finite, taken again by FMAs over the pixels of
@@ -182,7 +196,11 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
     const int per = strips * nblk, n = item / per, rem = item - n * per, rb = rem / strips, strip = rem - rb * strips;
     const int u0 = rb * th, u1 = min(H, u0 + th);
     const int x0 = strip * BM_COLS, xs = x0 - R;
-    const float sc = scale ? *scale : 1.f;
+    // the sums' scaling back goes into the caller's factor; one that this would make subnormal is applied when the walk
+    // is over (a second multiplication in the walk cost 1.5 % of the kernel)
+    const float factor = scale ? *scale : 1.f;
+    const bool after = factor != 0.f && !(fabsf(factor) >= 0x1p-78f);
+    const float sc = after ? 1.f : factor, down = sc * BM_DOWN;
     const size_t hw = (size_t)H * W;
     const float* gyn = gy + (size_t)n * F * hw;
     float* gxn = gx + (size_t)n * hw;
@@ -298,7 +316,7 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
         const int x = x0 + 8 * m;
         float big = 0.f;   // a NaN or an infinity stays in the sum
 #pragma unroll
-        for (int g = 0; g < 8; ++g) big += fabsf(o[g]), o[g] *= BM_DOWN;
+        for (int g = 0; g < 8; ++g) big += fabsf(o[g]);
         if (__ballot(mine && !(big < __builtin_inff()))) {
             bad0 = min(bad0, u);
             bad1 = u;
@@ -306,12 +324,12 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
         if (!mine) return;
         float* out = gxn + (size_t)u * W + x;
         if (x + 8 <= W) {
-            *reinterpret_cast<v4f_any*>(out) = sc * mk4(o[0], o[1], o[2], o[3]);
-            *reinterpret_cast<v4f_any*>(out + 4) = sc * mk4(o[4], o[5], o[6], o[7]);
+            *reinterpret_cast<v4f_any*>(out) = down * mk4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<v4f_any*>(out + 4) = down * mk4(o[4], o[5], o[6], o[7]);
         } else {
 #pragma unroll
             for (int g = 0; g < 8; ++g)
-                if (x + g < W) out[g] = sc * o[g];
+                if (x + g < W) out[g] = down * o[g];
         }
     };
 
@@ -334,10 +352,15 @@ __global__ __launch_bounds__(256, 2) void bank_bwd_in_mfma_k(const float* __rest
         bp = b;
         b = b + 1 == N ? 0 : b + 1;
     }
-    if (bad1 < 0) return;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the other lanes' sums are read back
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    bwd_in_again<R>(gyn, w, gxn, F, H, W, x0, bad0, bad1, sc);
+    if (bad1 < 0 && !after) return;
+    if (bad1 >= 0) {
+        own_writes();
+        bwd_in_again<R>(gyn, w, gxn, F, H, W, x0, bad0, bad1, sc);
+    }
+    if (after) {
+        own_writes();
+        bwd_in_times(gxn, W, x0, u0, u1, factor);
+    }
 }
 
 template <int R>

@@ -11,6 +11,9 @@ from oracle import oracle  # noqa: E402
 from paper_1605_06399_amd import synth  # noqa: E402
 from test_gpu_bank_input_mfma import cu, forced, index  # noqa: E402
 
+if gpu_available():
+    import torch
+
 F, H, W = 16, 24, 150
 
 
@@ -37,6 +40,16 @@ def problem(r, sg, sw):
 def test_small_and_large_operands(r, sg, sw):
     gy, w = problem(r, sg, sw)
     check(gy.astype(np.float32), w.astype(np.float32))
+
+
+@pytest.mark.parametrize("r", [3, 4])
+def test_callers_factor(r):
+    """The same products, the factor rounded into them once: factors around the smallest that takes the scaling in."""
+    gy, w = (a.astype(np.float32) for a in problem(r, 1.0, 1.0))
+    one = forced(index(), cu(gy), cu(w))
+    for f in (0.3, -7e20, 2.0 ** -78, 3e-24, -1e-30, 0.0):
+        got = forced(index(), cu(gy), cu(w), scale=torch.full((1,), f, device="cuda"))
+        assert np.array_equal(got, np.float32(f) * one), f
 
 
 @pytest.mark.parametrize("r", [3, 4])
